@@ -10,7 +10,7 @@
  *   - Return value: GT_OK (0) or a negative gt_status; gt_last_error() gives a
  *     thread-local message for the last failure on the calling thread.
  *   - The caller owns every buffer passed in (host and device). The library
- *     owns (a) one 2-word device buffer per GPU for the output comparison
+ *     owns (a) one 8 KiB device buffer per GPU for the output comparison
  *     (gt_compare and the searches' checks), allocated on its first use on
  *     that GPU and kept until gt_shutdown(), and (b) the M·N fp32 reference
  *     product of a search whose caller passes no c_ref (freed before the
@@ -174,13 +174,12 @@ int gt_compare(const void* C, const void* R, int64_t n, void* stream,
 
 /* gt_compare for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same result, with the two result words held in a static 256-byte
+ * the same result, with the partial results held in a static 8 KiB
  * device array of the library (one copy per GPU, kept until the process
  * ends) instead of the buffer gt_compare allocates on first use. No
- * hipMalloc, hipFree or other allocating call is made; n is not limited (the
- * kernels reduce any n into the two words). Calls that overlap on one GPU
- * race on that array; each call clears it before use. Synchronises the
- * stream. GT_EINVAL for null pointers or n < 1, GT_EHIP for a HIP failure. */
+ * hipMalloc, hipFree or other allocating call is made; n is not limited (at
+ * most 1024 blocks reduce any n). Calls that overlap on one GPU race on that
+ * array; each call writes what it reads back. Synchronises the stream. GT_EINVAL for null pointers or n < 1, GT_EHIP for a HIP failure. */
 int gt_compare_noalloc(const void* C, const void* R, int64_t n, void* stream,
                        double* rel);
 

@@ -7,14 +7,15 @@
 #include <mutex>
 #include <string>
 
+#include "aux_kernels.h"
 #include "internal.h"
 #include "runtime.h"
 
-// The comparison's two result words (max |C − R| and max |R| as ordered bit
-// patterns) live in words 0 and 1; 64 words (256 bytes) in all. Every call on
-// a GPU uses that GPU's copy: the comparison kernel's first launch clears the
-// two words, and calls that overlap on one GPU race on them.
-static __device__ __align__(256) unsigned scratch[64];
+// The comparison's partial results: a pair of words (max |C − R| and max |R|
+// as ordered bit patterns) per block of the reduction, 8 KiB. Every call on a
+// GPU uses that GPU's copy and writes every pair it reads back; calls that
+// overlap on one GPU race on them.
+static __device__ __align__(256) unsigned scratch[2 * gt::kCompareBlocks];
 
 namespace gt {
 namespace {

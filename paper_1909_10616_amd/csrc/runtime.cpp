@@ -149,22 +149,29 @@ int launch_lowered(const Lowered& lw, hipStream_t s) {
 
 namespace {
 std::mutex g_cmp_mu;
-unsigned* g_cmp_buf[64] = {};  // per device, 2 words, kept until process exit
+unsigned* g_cmp_buf[64] = {};  // per device, 2·kCompareBlocks words, kept until process exit
 }  // namespace
 
 int compare_into(const void* C, const void* R, int64_t n, unsigned* buf, hipStream_t s,
                  double* rel) {
-  hipError_t e =
-      launch_compare(static_cast<const float*>(C), static_cast<const float*>(R), n, buf, s);
+  int blocks = 0;
+  hipError_t e = launch_compare(static_cast<const float*>(C), static_cast<const float*>(R), n, buf,
+                                &blocks, s);
   if (e != hipSuccess) return hip_fail(e, "compare launch");
-  unsigned host[2];
-  e = hipMemcpyAsync(host, buf, sizeof(host), hipMemcpyDeviceToHost, s);
+  unsigned host[2 * kCompareBlocks];
+  e = hipMemcpyAsync(host, buf, 2 * sizeof(unsigned) * static_cast<size_t>(blocks),
+                     hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync (compare result)");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize (compare)");
+  unsigned ud = 0, ur = 0;
+  for (int b = 0; b < blocks; ++b) {
+    ud = std::max(ud, host[2 * b]);
+    ur = std::max(ur, host[2 * b + 1]);
+  }
   float md, mr;
-  std::memcpy(&md, &host[0], 4);
-  std::memcpy(&mr, &host[1], 4);
+  std::memcpy(&md, &ud, 4);
+  std::memcpy(&mr, &ur, 4);
   if (std::isnan(md))
     *rel = NAN;
   else if (mr == 0.0f)
@@ -182,12 +189,11 @@ int compare_on_gpu(const void* C, const void* R, int64_t n, hipStream_t s, doubl
     set_error("device index out of range");
     return GT_EINVAL;
   }
-  // The device's 2-word result buffer is held from its clear to the copy
-  // back: comparisons from several threads (any streams) take turns, and
+  // The device's result buffer is held from the launch to the copy back: comparisons from several threads (any streams) take turns, and
   // gt_shutdown cannot free the buffer under one in flight.
   std::lock_guard<std::mutex> lk(g_cmp_mu);
   if (!g_cmp_buf[dev]) {
-    e = hipMalloc(&g_cmp_buf[dev], 2 * sizeof(unsigned));
+    e = hipMalloc(&g_cmp_buf[dev], 2 * kCompareBlocks * sizeof(unsigned));
     if (e != hipSuccess) return hip_fail(e, "hipMalloc (compare result)");
   }
   return compare_into(C, R, n, g_cmp_buf[dev], s, rel);

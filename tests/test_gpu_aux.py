@@ -1,0 +1,54 @@
+"""The helper kernels of the searches' output check at the sizes where their
+work splits: the comparison (one partial result per block, 16-byte and scalar
+loads, remainders, NaN and infinities)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gt():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_1909_10616_amd import gemmtune
+    gemmtune.lib()
+    return gemmtune
+
+
+def _expected(c, r):
+    """max|c − r| / max|r| from fp32 differences; the largest |r| skips NaN."""
+    with np.errstate(invalid="ignore"):
+        d = np.abs(c - r)
+    if np.isnan(d).any():
+        return math.nan
+    md, mr = float(d.max()), float(np.nanmax(np.abs(r)))
+    return (0.0 if md == 0 else math.inf) if mr == 0 else md / mr
+
+
+# one thread's share and its neighbours, one block's, and more than the most
+# blocks (1024 of 4096 elements) with a remainder of 1, 2 and 3
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 255, 1023, 4095, 4096, 4097, 65537, (1 << 22) - 1,
+                               (1 << 22) + 3])
+@pytest.mark.parametrize("offsets", [(0, 0), (1, 0), (1, 1), (4, 8)])
+def test_compare_at_block_and_alignment_edges(gt, n, offsets):
+    rng = np.random.default_rng(n)
+    r = rng.standard_normal(n + 16).astype(np.float32)
+    c = r + (1e-4 * rng.standard_normal(n + 16)).astype(np.float32)
+    co, ro = offsets
+    for where in sorted({0, n // 2, n - 1}):
+        for side, value in ((None, 0.0), ("c", np.nan), ("c", np.inf), ("c", 7.0), ("r", np.nan),
+                            ("r", -9.0)):
+            cc, rr = c.copy(), r.copy()
+            if side == "c":
+                cc[co + where] = value
+            elif side == "r":
+                rr[ro + where] = value
+            cd, rd = torch.from_numpy(cc).cuda(), torch.from_numpy(rr).cuda()
+            want = _expected(cc[co:co + n], rr[ro:ro + n])
+            for f in (gt.gt_compare, gt.gt_compare_noalloc):
+                got = f(cd[co:co + n], rd[ro:ro + n])
+                assert got == want or (math.isnan(got) and math.isnan(want)), (where, side, value)
