@@ -157,8 +157,8 @@ int gt_measure(const gt_config* cfg, const void* A, const void* B, void* C,
                int warmup, int runs, double abort_ms, double* mean_ms,
                double* first_ms, int* aborted);
 
-/* Plain (non-MFMA, one thread per output, any M and N) GPU product in fp32,
- * used by the search as the reference its candidates are checked against.
+/* Plain (non-MFMA, any M and N) GPU product in fp32, each output one chain of
+ * fused multiply-adds with k ascending, used by the search as the reference its candidates are checked against.
  * Same operands and layouts as gemm_run (dtype may carry GT_A_KMAJOR); C is
  * caller-owned M·N fp32. Asynchronous. Errors: GT_EINVAL (null pointer,
  * M, N or K below 1, unknown dtype), GT_EHIP (launch failure). */

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "aux_kernels.h"
 
@@ -23,25 +24,108 @@ __device__ __forceinline__ float load_in(const void* p, int64_t i, int dtype) {
   return __builtin_bit_cast(float, bits);
 }
 
-// One thread per output (grid-stride over rows and columns, so any M and N
-// fit the grid's limits); k ascending, fp32 fused multiply-add. dtype 0/1
-// (fp32/bf16), plus 16 when A is K-major (element (m, k) at A[k·M + m]).
-__global__ void reference_kernel(const void* __restrict__ A, const void* __restrict__ B,
-                                 float* __restrict__ C, int64_t M, int64_t N, int64_t K,
-                                 int dtype) {
-  const int dt = dtype & 15;
-  const int64_t sr = (dtype & 16) ? 1 : K, sk = (dtype & 16) ? M : 1;
-  const int64_t rstep = static_cast<int64_t>(gridDim.y) * blockDim.y;
-  const int64_t cstep = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t row = static_cast<int64_t>(blockIdx.y) * blockDim.y + threadIdx.y; row < M;
-       row += rstep)
-    for (int64_t col = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; col < N;
-         col += cstep) {
-      float s = 0.0f;
-      for (int64_t l = 0; l < K; ++l)
-        s = fmaf(load_in(A, row * sr + l * sk, dt), load_in(B, l * N + col, dt), s);
-      C[row * N + col] = s;
+// The check product: a T×T tile of C per 256 threads (16×16, each thread
+// R = T/16 rows and columns of it), K in chunks of KC through LDS as fp32.
+// Every output is one chain of fp32 fused multiply-adds with k ascending,
+// whatever the tile, so the values do not depend on it. It stays off the
+// matrix cores: what it checks runs there.
+// Bound by fp32 VALU issue (one FMA per lane and 4 cycles without packed
+// instructions, 78.6 TFLOP/s): R·R FMAs against 2·R LDS values per k. 4096³
+// bf16: 42.6 ms with one thread per output reading A and B through the
+// caches, 1.75 ms (78 TFLOP/s) with 128×128 tiles; 1024³ 0.47 -> 0.10 ms. Rows,
+// columns and k past the edges are clamped for the loads (any size, any
+// alignment, scalar coalesced loads: 2·T·KC of them per T·T·KC FMAs) and
+// their products are not formed (k) or not stored (rows, columns).
+// AK: A is K-major (element (m, k) at A[k·M + m]).
+constexpr int kRefKC = 16;
+
+template <int DT, bool AK, int T>
+__global__ void __launch_bounds__(256)
+    reference_kernel(const void* __restrict__ Av, const void* __restrict__ Bv,
+                     float* __restrict__ C, int64_t M, int64_t N, int64_t K, int64_t tilesN,
+                     int64_t tiles) {
+  constexpr int KC = kRefKC, R = T / 16, LD = T + 4, NL = T * KC / 256;
+  constexpr int V = R < 4 ? R : 4, NV = R / V;  // a thread's rows: NV runs of V, T/NV apart
+  __shared__ __align__(16) float as[2][KC][LD], bs[2][KC][LD];
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  constexpr int KS = 256 / T;  // k rows one pass of [k][T] loads covers
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t row0 = tile / tilesN * T, col0 = tile % tilesN * T;
+    // element offsets of this thread's loads at k = 0; load i of a chunk is
+    // row (tid / 16) + 16·i, k tid % 16 of a row-major A, and column tid % T,
+    // k tid / T + KS·i of B (and of a K-major A)
+    const int64_t bcol = min(col0 + tid % T, N - 1);
+    int64_t arow[AK ? 1 : NL];
+    if constexpr (AK) {
+      arow[0] = min(row0 + tid % T, M - 1);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) arow[i] = min(row0 + ty + 16 * i, M - 1) * K;
     }
+    float ra[NL], rb[NL];
+    auto gload = [&](int64_t k0) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int64_t kb = min(k0 + tid / T + KS * i, K - 1);
+        rb[i] = load_in(Bv, kb * N + bcol, DT);
+        if constexpr (AK)
+          ra[i] = load_in(Av, kb * M + arow[0], DT);
+        else
+          ra[i] = load_in(Av, arow[i] + min(k0 + tx, K - 1), DT);
+      }
+    };
+    auto lstore = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        bs[buf][tid / T + KS * i][tid % T] = rb[i];
+        if constexpr (AK)
+          as[buf][tid / T + KS * i][tid % T] = ra[i];
+        else
+          as[buf][tx][ty + 16 * i] = ra[i];
+      }
+    };
+    float acc[R][R];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j) acc[i][j] = 0.0f;
+    auto step = [&](int buf, int kk) __attribute__((always_inline)) {
+      float a[R], b[R];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        __builtin_memcpy(a + v * V, &as[buf][kk][v * (T / NV) + ty * V], V * 4);
+        __builtin_memcpy(b + v * V, &bs[buf][kk][v * (T / NV) + tx * V], V * 4);
+      }
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    };
+    gload(0);
+    lstore(0);
+    __syncthreads();
+    int buf = 0;
+    int64_t k0 = 0;
+    for (; k0 + KC < K; k0 += KC, buf ^= 1) {
+      gload(k0 + KC);
+#pragma unroll
+      for (int kk = 0; kk < KC; ++kk) step(buf, kk);
+      lstore(buf ^ 1);
+      __syncthreads();
+    }
+    const int left = static_cast<int>(K - k0);
+    for (int kk = 0; kk < left; ++kk) step(buf, kk);
+    __syncthreads();  // the next tile's first store reuses a buffer
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int64_t r = row0 + i / V * (T / NV) + ty * V + i % V;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int64_t c = col0 + j / V * (T / NV) + tx * V + j % V;
+        if (r < M && c < N) C[r * N + c] = acc[i][j];
+      }
+    }
+  }
 }
 
 // out[2b], out[2b + 1] = block b's max |C − R| and max |R| as bits
@@ -115,14 +199,41 @@ hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
+namespace {
+
+template <int DT, bool AK>
+void launch_reference_tiled(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
+                            hipStream_t s) {
+  // The largest tile that leaves a workgroup or more for each of the 256
+  // compute units, else the smallest.
+  const auto tiles = [&](int64_t t) { return (M + t - 1) / t * ((N + t - 1) / t); };
+  const auto run = [&](auto tag) {
+    constexpr int T = decltype(tag)::value;
+    const int64_t nt = tiles(T);
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>(nt, int64_t{1} << 20)));
+    hipLaunchKernelGGL((reference_kernel<DT, AK, T>), grid, dim3(256), 0, s, A, B, C, M, N, K,
+                       (N + T - 1) / T, nt);
+  };
+  if (tiles(128) >= 256)
+    run(std::integral_constant<int, 128>{});
+  else if (tiles(64) >= 256)
+    run(std::integral_constant<int, 64>{});
+  else
+    run(std::integral_constant<int, 32>{});
+}
+
+}  // namespace
+
 hipError_t launch_reference(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
                             int dtype, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;  // an empty C: nothing to write
-  const dim3 block(64, 4);
-  // grid.y is limited to 65535 blocks; the kernel strides over what is left
-  const dim3 grid(static_cast<unsigned>(std::min<int64_t>((N + 63) / 64, int64_t{1} << 20)),
-                  static_cast<unsigned>(std::min<int64_t>((M + 3) / 4, 65535)));
-  hipLaunchKernelGGL(reference_kernel, grid, block, 0, s, A, B, C, M, N, K, dtype);
+  const bool ak = (dtype & 16) != 0;
+  if ((dtype & 15) == 0)
+    ak ? launch_reference_tiled<0, true>(A, B, C, M, N, K, s)
+       : launch_reference_tiled<0, false>(A, B, C, M, N, K, s);
+  else
+    ak ? launch_reference_tiled<1, true>(A, B, C, M, N, K, s)
+       : launch_reference_tiled<1, false>(A, B, C, M, N, K, s);
   return hipGetLastError();
 }
 

@@ -1,6 +1,7 @@
 """The helper kernels of the searches' output check at the sizes where their
 work splits: the comparison (one partial result per block, 16-byte and scalar
-loads, remainders, NaN and infinities)."""
+loads, remainders, NaN and infinities) and the check product (three tile
+sizes, ragged edges)."""
 import math
 
 import numpy as np
@@ -52,3 +53,25 @@ def test_compare_at_block_and_alignment_edges(gt, n, offsets):
             for f in (gt.gt_compare, gt.gt_compare_noalloc):
                 got = f(cd[co:co + n], rd[ro:ro + n])
                 assert got == want or (math.isnan(got) and math.isnan(want)), (where, side, value)
+
+
+# tile edges of each tile size (32, 64 and 128 outputs a side; 256 tiles or
+# more pick the larger), one row or column past them, and K around a chunk of
+# 16 and below it
+REFERENCE = [(1, 1, 1), (31, 33, 15), (32, 32, 16), (33, 31, 17), (65, 1, 33), (1024, 1024, 5),
+             (993, 1025, 19), (1025, 993, 16), (2048, 2048, 3), (2049, 1921, 18), (1921, 2049, 1)]
+
+
+@pytest.mark.parametrize("kmajor", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", REFERENCE)
+def test_reference_product_at_tile_edges(gt, orc, shape, dtype, kmajor):
+    """Small integers, exact in any order: every element equals the oracle's."""
+    from workloads import make_inputs, raw_bytes
+    M, N, K = shape
+    A, B = make_inputs(M, N, K, dtype, 17, "smallint")
+    ref = orc.gemm(raw_bytes(A), raw_bytes(B), M, N, K, dtype)
+    Ad = (A.t().contiguous() if kmajor else A).cuda()
+    C = torch.full((M, N), float("nan"), device="cuda")
+    gt.gt_reference_gemm(Ad, B.cuda(), C, a_kmajor=kmajor)
+    assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
