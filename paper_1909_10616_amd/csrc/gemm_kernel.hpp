@@ -10,9 +10,11 @@
 //   generic — any legitimate configuration; blocks smaller than the MFMA
 //             instruction are zero-padded in registers, LDS holds the natural
 //             row-major tiles;
-//   fast    — blocks that are multiples of the instruction: 16-byte global
-//             loads staged through registers one stage ahead, B transposed in
-//             registers so every LDS fragment read is one 16-byte read, LDS
+//   fast    — blocks that are multiples of the instruction, direct
+//             global→LDS loads into a ring of stages: bf16 (gemm_fast_dl) and
+//             fp32 (gemm_ring_f32). bf16 tiles the ring cannot serve stage
+//             16-byte loads through registers one stage ahead (gemm_fast), B
+//             transposed there so every LDS fragment read is 16 bytes, LDS
 //             tiles XOR-swizzled by 128-byte line to avoid bank conflicts.
 // Everything else (grid, waves, block extents, stage depth, split-K, double
 // buffering) is a runtime argument.
@@ -46,6 +48,7 @@ struct KArgs {
   int32_t ns;              // ring stages (direct-load path)
   int32_t aKM;             // A given K-major (K×M row-major, element (m, k) at A[k·M + m])
   int32_t lgBM;
+  int32_t wide;            // fp32 ring: a stage's offsets from its origins exceed 32 bits
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -129,6 +132,35 @@ __device__ __forceinline__ void put(bool atomic, float* p, float v) {
     unsafeAtomicAdd(p, v);
   else
     *p = v;
+}
+
+// Writes a wavefront's accumulators: TM × TN tiles of I×I from Cw, the
+// wavefront tile's origin in C. One 64-bit address per row, stepped by N, and
+// one branch for the atomic form: with the address and the branch of every
+// element worked out on its own, an element cost about ten instructions.
+template <int I, int TM, int TN, typename acc_t>
+__device__ __forceinline__ void store_tile(const KArgs& a, float* Cw, int lane,
+                                           const acc_t (&acc)[TM][TN]) {
+  const int64_t N = a.N;
+  float* const first = Cw + static_cast<int64_t>(out_row<I>(lane, 0)) * N + lane % I;
+  auto rows = [&](auto put_one) __attribute__((always_inline)) {
+    float* p = first;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int e = 0; e < AccT<I>::N; ++e) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) put_one(p + j * I, acc[i][j][e]);
+        // the lane's next row: the accumulator's, or the next tile's first
+        const int here = out_row<I>(0, e);
+        p += (e + 1 < AccT<I>::N ? out_row<I>(0, e + 1) - here : I - here) * N;
+      }
+    }
+  };
+  if (a.atomic)
+    rows([](float* p, float v) __attribute__((always_inline)) { unsafeAtomicAdd(p, v); });
+  else
+    rows([](float* p, float v) __attribute__((always_inline)) { *p = v; });
 }
 
 // ---------------------------------------------------------------------------
@@ -305,7 +337,7 @@ __device__ void gemm_generic(const KArgs& a, char* smem) {
 }
 
 // ---------------------------------------------------------------------------
-// Fast path
+// Register-staged fast path (bf16)
 // ---------------------------------------------------------------------------
 
 // 16-byte chunk q of a tile → its LDS slot: XOR inside each 128-byte line
@@ -316,29 +348,19 @@ __device__ __forceinline__ int swz(int q) { return q ^ (((q >> 3) ^ (q >> 6)) & 
 constexpr int kPfA = 8;  // A chunks staged in registers per thread
 constexpr int kPfB = 1;  // B VEC×VEC blocks staged per thread
 
-// Transpose a VEC×VEC block held as VEC row chunks into VEC column chunks.
-template <int DT>
+// Transpose an 8×8 block of 16-bit values held as row chunks into column
+// chunks; dword w of a chunk holds elements 2w (low), 2w+1 (high).
 __device__ __forceinline__ void transpose_block(const u32x4* in, u32x4* out) {
-  if constexpr (DT == 1) {
-    // 8×8 of 16-bit values; dword w of a chunk holds elements 2w (low), 2w+1 (high)
-    const uint32_t* r = reinterpret_cast<const uint32_t*>(in);  // r[j*4 + w]
-    uint32_t* o = reinterpret_cast<uint32_t*>(out);
+  const uint32_t* r = reinterpret_cast<const uint32_t*>(in);  // r[j*4 + w]
+  uint32_t* o = reinterpret_cast<uint32_t*>(out);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < 4; ++u) {
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint32_t lo = r[(2 * w) * 4 + u], hi = r[(2 * w + 1) * 4 + u];
-        o[(2 * u) * 4 + w] = (lo & 0xffffu) | (hi << 16);
-        o[(2 * u + 1) * 4 + w] = (lo >> 16) | (hi & 0xffff0000u);
-      }
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t lo = r[(2 * w) * 4 + u], hi = r[(2 * w + 1) * 4 + u];
+      o[(2 * u) * 4 + w] = (lo & 0xffffu) | (hi << 16);
+      o[(2 * u + 1) * 4 + w] = (lo >> 16) | (hi & 0xffff0000u);
     }
-  } else {
-    const float* r = reinterpret_cast<const float*>(in);
-    float* o = reinterpret_cast<float*>(out);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) o[t * 4 + j] = r[j * 4 + t];
   }
 }
 
@@ -350,15 +372,13 @@ constexpr int ilog2c() {
 // CPR = 16-byte chunks per LDS row = BK / VEC, a compile-time constant so
 // that the chunk-step loop unrolls: the fragments of chunk-step cs+1 are read
 // from LDS while the MFMAs of chunk-step cs run.
-// AK: A given K-major; its tile is loaded like B's (VEC×VEC blocks,
-// transposed in registers) into the same [m][k-chunk] LDS layout.
-template <int DT, int I, int TM, int TN, int CPR, bool AK = false>
+template <int I, int TM, int TN, int CPR>
 __device__ void gemm_fast(const KArgs& a, char* smem) {
-  using T = typename Elem<DT>::T;
+  using T = Elem<1>::T;
   using acc_t = typename AccT<I>::type;
   constexpr int NACC = AccT<I>::N;
-  constexpr int VEC = Elem<DT>::VEC;
-  constexpr int LGV = VEC == 8 ? 3 : 2;
+  constexpr int VEC = Elem<1>::VEC;
+  constexpr int LGV = 3;
   constexpr int G = 64 / I;          // lane groups of an MFMA operand
   constexpr int NCS = CPR / G;       // chunk-steps per stage
   constexpr int LGCPR = ilog2c<CPR>();
@@ -380,8 +400,7 @@ __device__ void gemm_fast(const KArgs& a, char* smem) {
   const int stage = achunks + (a.BN << LGCPR);  // chunks per stage
   u32x4* lds = reinterpret_cast<u32x4*>(smem);
 
-  const T* Ag = reinterpret_cast<const T*>(a.A) +
-                (AK ? static_cast<int64_t>(gm) * a.BM : static_cast<int64_t>(gm) * a.BM * a.K);
+  const T* Ag = reinterpret_cast<const T*>(a.A) + static_cast<int64_t>(gm) * a.BM * a.K;
   const T* Bg = reinterpret_cast<const T*>(a.B) + static_cast<int64_t>(gn) * a.BN;
 
   const int rounds = max((achunks + nthr * kPfA - 1) / (nthr * kPfA),
@@ -410,45 +429,16 @@ __device__ void gemm_fast(const KArgs& a, char* smem) {
     bq0[i] = ((nb << LGV) << LGCPR) + kb;
   }
 
-  // K-major A: blocks of VEC k-rows × VEC m (one 16-byte chunk per row),
-  // kPfA / VEC of them per thread in the staging registers
-  constexpr int kPfAB = kPfA / VEC;
-  const int lgnbm = a.lgBM - LGV;
-  const int ablocks = CPR << lgnbm;
-  const int nab = __builtin_amdgcn_readfirstlane(min(kPfAB, (ablocks + nthr - 1) / nthr));
-  int64_t aoffk[kPfAB > 0 ? kPfAB : 1];
-  int aq0[kPfAB > 0 ? kPfAB : 1];
-  if constexpr (AK) {
-#pragma unroll
-    for (int i = 0; i < kPfAB; ++i) {
-      const int b = min(tid + i * nthr, ablocks - 1);
-      const int nm = b & ((1 << lgnbm) - 1), kb = b >> lgnbm;
-      aoffk[i] = static_cast<int64_t>(kb << LGV) * a.M + (nm << LGV);
-      aq0[i] = ((nm << LGV) << LGCPR) + kb;
-    }
-  }
-
   u32x4 ra[kPfA];
   u32x4 rb[kPfB * VEC];
 
   auto gload = [&](int l) __attribute__((always_inline)) {
     const int64_t kbase = (static_cast<int64_t>(l) * a.kSplit + z) * a.BK;
     const T* bg = Bg + kbase * a.N;
-    if constexpr (AK) {
-      const T* ag = Ag + kbase * a.M;
+    const T* ag = Ag + kbase + aoff0;
 #pragma unroll
-      for (int i = 0; i < kPfAB; ++i)
-        if (i < nab) {
-#pragma unroll
-          for (int j = 0; j < VEC; ++j)
-            ra[i * VEC + j] = *reinterpret_cast<const u32x4*>(ag + aoffk[i] + j * a.M);
-        }
-    } else {
-      const T* ag = Ag + kbase + aoff0;
-#pragma unroll
-      for (int i = 0; i < kPfA; ++i)
-        if (i < na) ra[i] = *reinterpret_cast<const u32x4*>(ag + i * astride);
-    }
+    for (int i = 0; i < kPfA; ++i)
+      if (i < na) ra[i] = *reinterpret_cast<const u32x4*>(ag + i * astride);
 #pragma unroll
     for (int i = 0; i < kPfB; ++i)
       if (i < nbb) {
@@ -461,25 +451,14 @@ __device__ void gemm_fast(const KArgs& a, char* smem) {
   auto lstore = [&](int buf) __attribute__((always_inline)) {
     u32x4* as = lds + buf * stage;
     u32x4* bs = as + achunks;
-    if constexpr (AK) {
 #pragma unroll
-      for (int i = 0; i < kPfAB; ++i)
-        if (i < nab) {
-          u32x4 t[VEC];
-          transpose_block<DT>(&ra[i * VEC], t);
-#pragma unroll
-          for (int j = 0; j < VEC; ++j) as[swz(aq0[i] + (j << LGCPR))] = t[j];
-        }
-    } else {
-#pragma unroll
-      for (int i = 0; i < kPfA; ++i)
-        if (i < na) as[swz(ta + i * nthr)] = ra[i];
-    }
+    for (int i = 0; i < kPfA; ++i)
+      if (i < na) as[swz(ta + i * nthr)] = ra[i];
 #pragma unroll
     for (int i = 0; i < kPfB; ++i)
       if (i < nbb) {
         u32x4 t[VEC];
-        transpose_block<DT>(&rb[i * VEC], t);
+        transpose_block(&rb[i * VEC], t);
 #pragma unroll
         for (int j = 0; j < VEC; ++j) bs[swz(bq0[i] + (j << LGCPR))] = t[j];
       }
@@ -490,29 +469,16 @@ __device__ void gemm_fast(const KArgs& a, char* smem) {
     const int64_t kbase = (static_cast<int64_t>(l) * a.kSplit + z) * a.BK;
     u32x4* as = lds + buf * stage;
     u32x4* bs = as + achunks;
-    if constexpr (AK) {
-      for (int b = tid; b < ablocks; b += nthr) {
-        const int nm = b & ((1 << lgnbm) - 1), kb = b >> lgnbm;
-        const T* src = Ag + (kbase + (kb << LGV)) * a.M + (nm << LGV);
-        u32x4 r[VEC], t[VEC];
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) r[j] = *reinterpret_cast<const u32x4*>(src + j * a.M);
-        transpose_block<DT>(r, t);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) as[swz((((nm << LGV) + j) << LGCPR) + kb)] = t[j];
-      }
-    } else {
-      for (int e = tid; e < achunks; e += nthr)
-        as[swz(e)] = *reinterpret_cast<const u32x4*>(
-            Ag + static_cast<int64_t>(e >> LGCPR) * a.K + kbase + ((e & (CPR - 1)) << LGV));
-    }
+    for (int e = tid; e < achunks; e += nthr)
+      as[swz(e)] = *reinterpret_cast<const u32x4*>(
+          Ag + static_cast<int64_t>(e >> LGCPR) * a.K + kbase + ((e & (CPR - 1)) << LGV));
     for (int b = tid; b < bblocks; b += nthr) {
       const int nb = b & ((1 << lgnbn) - 1), kb = b >> lgnbn;
       const T* src = Bg + (kbase + (kb << LGV)) * a.N + (nb << LGV);
       u32x4 r[VEC], t[VEC];
 #pragma unroll
       for (int j = 0; j < VEC; ++j) r[j] = *reinterpret_cast<const u32x4*>(src + j * a.N);
-      transpose_block<DT>(r, t);
+      transpose_block(r, t);
 #pragma unroll
       for (int j = 0; j < VEC; ++j) bs[swz((((nb << LGV) + j) << LGCPR) + kb)] = t[j];
     }
@@ -555,23 +521,12 @@ __device__ void gemm_fast(const KArgs& a, char* smem) {
     for (int t = 0; t < TN; ++t) fb[slot][t] = bs[(xb[t][j] ^ (c & 7)) + (c & ~7)];
   };
   auto mfmas = [&](int slot) __attribute__((always_inline)) {
-    if constexpr (DT == 1) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = mfma_bf16(__builtin_bit_cast(bf16x8, fa[slot][i]),
-                                __builtin_bit_cast(bf16x8, fb[slot][j]), acc[i][j]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = mfma_f32(__builtin_bit_cast(f32x4, fa[slot][i])[q],
-                                 __builtin_bit_cast(f32x4, fb[slot][j])[q], acc[i][j]);
-    }
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = mfma_bf16(__builtin_bit_cast(bf16x8, fa[slot][i]),
+                              __builtin_bit_cast(bf16x8, fb[slot][j]), acc[i][j]);
   };
 
   auto compute = [&](const u32x4* as) __attribute__((always_inline)) {
@@ -741,6 +696,21 @@ __device__ __forceinline__ void dma_load16(uint32_t off, uint64_t base, uint32_t
                : "memory", "m0");
 }
 
+// The same when n (a uniform value) is above i, and otherwise with no lane
+// enabled: the instruction then moves nothing but still counts in vmcnt. A
+// scalar select instead of a branch. (The instructions after the write of m0
+// also keep it the one wait state ahead of the load that the ISA asks for.)
+__device__ __forceinline__ void dma_load16_if(int n, int i, uint32_t off, uint64_t base,
+                                              uint32_t lds_base) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\ts_cmp_gt_i32 %3, %4\n\ts_cselect_b64 exec, -1, 0\n\t"
+      "global_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+      :
+      : "v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(static_cast<int>(lds_base))),
+        "s"(__builtin_amdgcn_readfirstlane(n)), "n"(i)
+      : "memory", "m0", "scc");
+}
+
 // A wavefront-uniform pointer as a 64-bit scalar (each half taken from the
 // first active lane and zero-extended).
 __device__ __forceinline__ uint64_t uniform_ptr(const void* p) {
@@ -754,6 +724,13 @@ __device__ __forceinline__ uint64_t uniform_ptr(const void* p) {
 __device__ __forceinline__ uint32_t lds_off(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
       (const __attribute__((address_space(3))) char*)(p)));
+}
+
+// Workgroup barrier that no LDS access is moved across.
+__device__ __forceinline__ void ring_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 template <int I, int TM, int TN, int CPR>
@@ -1079,6 +1056,381 @@ __device__ __forceinline__ void gemm_fast_dl(const KArgs& a, char* smem) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// fp32 fast path: direct global→LDS loads into a ring
+// ---------------------------------------------------------------------------
+//
+// Tiles reach LDS by global_load_lds_dwordx4 (64 consecutive 16-byte slots a
+// wavefront instruction), never through registers, into a ring of ns stages
+// that keeps ns − 1 stages of loads in flight; one barrier a stage.
+// A row-major: [m][k] chunks of 4 k, row r's chunks XOR-ed by fswz(r), read 16
+// bytes a lane: the 4 k of a chunk feed 4 MFMAs, lane group g holding chunk
+// cs·G + g. B (and a K-major A) keep their [k][n] rows, split into one panel
+// per wavefront column of WN = TN·I columns so that every row stride is a
+// compile-time constant; a lane reads its column of the same 4 k with 4-byte
+// reads (consecutive lanes, consecutive banks). fp32 MFMAs take 32 (16×16×4)
+// or 64 cycles (32×32×2), so the extra LDS instructions that the untransposed
+// B costs stay below the matrix pipe's time: with one wavefront a SIMD and one
+// MFMA tile each, 16 of 128 (16×16) or 256 (32×32) cycles per chunk-step.
+// With 16×16 MFMA the two lane groups of a half-wavefront read rows 4 apart,
+// a multiple of 256 bytes: odd groups' 16 columns are stored in the other half
+// of a 128-byte line (panels of 32 columns or more).
+//
+// Bound by the fp32 matrix pipe (157 TFLOP/s) where the tiles fill the chip,
+// by the launch and one trip to memory (about 5 µs) where K is short. Against
+// the register-staged form it replaced (loads one stage ahead, transposed in
+// registers, spilled from 64 accumulators on): 2048³ 158 -> 128 µs
+// (134 TFLOP/s), 1024³ 30.6 -> 23.0 µs, K-major 28.6 -> 21.5 µs,
+// 128×2048×2048 in 32×32×32 tiles 44.7 -> 24.6 µs.
+
+// XOR of a row-major A row's chunk index: 8 consecutive rows read at the same
+// chunk hit the 8 distinct 16-byte slots of 128 bytes.
+template <int CPR>
+__device__ __forceinline__ int fswz(int row) {
+  return (row >> (CPR >= 8 ? 0 : (CPR == 4 ? 1 : 2))) & ((CPR < 8 ? CPR : 8) - 1);
+}
+
+// Whether a [k][n] panel of CW chunks a row stores the rows k with bit 2 set
+// with the halves of each 128 bytes swapped: with 16×16 MFMA, where every lane
+// holds rows of one instruction and the swap is the same for all of them or
+// alternates (panels of 32 and 64 columns; wider ones, of 8 MFMA tiles a
+// wavefront or more, keep the 2-way conflict).
+template <int I, int CW>
+constexpr bool flip_panel() {
+  return I == 16 && (CW == 8 || CW == 16);
+}
+
+// Whether some wavefront layout (powers of two, up to 8 wavefronts) of this
+// kernel has nh / 2 < (the most loads of one operand per wavefront) ≤ nh, or
+// at most 2 for nh = 2.
+template <int I, int TM, int TN, int CPR>
+constexpr bool ring_needs(int nh) {
+  for (int wm = 1; wm <= 8; wm *= 2)
+    for (int wn = 1; wm * wn <= 8; wn *= 2) {
+      const int na = (wm * TM * I * CPR / 64 + wm * wn - 1) / (wm * wn);
+      const int nb = (wn * TN * I * CPR / 64 + wm * wn - 1) / (wm * wn);
+      const int most = na > nb ? na : nb;
+      if (most <= nh && (nh == 2 || most > nh / 2)) return true;
+    }
+  return false;
+}
+
+template <int I, int TM, int TN, int CPR, bool AK>
+__device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
+  using acc_t = typename AccT<I>::type;
+  constexpr int G = 64 / I;
+  constexpr int NCS = CPR / G;  // chunk-steps per stage
+  constexpr int LGCPR = ilog2c<CPR>();
+  constexpr int BK = CPR * 4;
+  constexpr int WM = TM * I, WN = TN * I;
+  static_assert(NCS >= 1, "stage shallower than one MFMA K step");
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = blockDim.x >> 6;
+  const int wm = wave % a.wavesM;
+  const int wn = wave / a.wavesM;
+  int gm, gn;
+  tile_of(a, gm, gn);
+  const int z = blockIdx.y;
+  const int BM = a.BM, BN = a.BN, ns = a.ns;
+  const uint32_t bbase = static_cast<uint32_t>(BM << LGCPR) * 16u;  // B inside a slot, bytes
+  const uint32_t stage16 = bbase + (static_cast<uint32_t>(BN << LGCPR) * 16u);
+  const uint32_t lds0 = static_cast<uint32_t>(
+      __builtin_amdgcn_readfirstlane(static_cast<int>(lds_off(smem))));
+
+  // Origins of this workgroup's tiles in bytes, and the strides of consecutive
+  // stages of this split-K slice.
+  const uint64_t lda = static_cast<uint64_t>(AK ? a.M : a.K) * 4u;
+  const uint64_t ldb = static_cast<uint64_t>(a.N) * 4u;
+  const uint64_t stepA = static_cast<uint64_t>(a.kSplit) * BK * (AK ? lda : 4u);
+  const uint64_t stepB = static_cast<uint64_t>(a.kSplit) * BK * ldb;
+  const uint64_t orgA = uniform_ptr(a.A) + static_cast<uint64_t>(gm) * BM * (AK ? 4u : lda) +
+                        static_cast<uint64_t>(z) * BK * (AK ? lda : 4u);
+  const uint64_t orgB = uniform_ptr(a.B) + static_cast<uint64_t>(gn) * BN * 4u +
+                        static_cast<uint64_t>(z) * BK * ldb;
+
+  // This wavefront's share of one operand's loads of a stage: instructions
+  // b0, b0 + db, … of a block of rows of C chunks (a row-major A's tile, rows
+  // of CPR chunks of k; a panel, rows of W / 4 chunks of columns). Instruction
+  // b covers chunks 64·b … 64·b + 63 of the block.
+  struct Share {
+    int cnt, b0, db;
+    uint32_t row, pos;  // per lane: its row's and chunk's bytes past the instruction's first
+    uint64_t base;      // the block's bytes from the stage's origin
+    uint32_t dst;       // … and from the slot's start
+  };
+  // Row-major A.
+  auto share_rows = [&](int w) __attribute__((always_inline)) {
+    Share h;
+    h.cnt = (((BM << LGCPR) >> 6) - w + nw - 1) / nw;
+    h.b0 = w;
+    h.db = nw;
+    h.row = static_cast<uint32_t>(lane >> LGCPR) * static_cast<uint32_t>(lda);
+    h.pos = static_cast<uint32_t>((lane & (CPR - 1)) ^ fswz<CPR>(lane >> LGCPR)) * 16u;
+    h.base = 0;
+    h.dst = 0;
+    return h;
+  };
+  // A [k][n] operand in `panels` (at most nw) panels of W columns, one after
+  // the other in LDS: consecutive wavefronts take the same rows of consecutive
+  // panels, then the next rows.
+  auto share_panels = [&](int w, int panels, uint64_t ld, auto wtag) __attribute__((always_inline)) {
+    constexpr int CW = decltype(wtag)::value / 4;  // chunks per row of a panel
+    constexpr int NPP = BK * CW / 64;              // instructions per panel
+    Share h;
+    const int panel = w % panels;
+    h.b0 = w / panels;
+    h.db = nw / panels;
+    h.cnt = (NPP - h.b0 + h.db - 1) / h.db;
+    const int pos = CW >= 64 ? lane : lane % CW, row = CW >= 64 ? 0 : lane / CW;
+    h.row = static_cast<uint32_t>(row) * static_cast<uint32_t>(ld);
+    h.pos = static_cast<uint32_t>(flip_panel<I, CW>() ? pos ^ (row & 4) : pos) * 16u;
+    h.base = static_cast<uint64_t>(panel * CW) * 16u;
+    h.dst = static_cast<uint32_t>(panel * NPP) * 1024u;
+    return h;
+  };
+  constexpr std::integral_constant<int, WM> wm_tag{};
+  constexpr std::integral_constant<int, WN> wn_tag{};
+  Share ha;
+  if constexpr (AK)
+    ha = share_panels(wave, a.wavesM, lda, wm_tag);
+  else
+    ha = share_rows(wave);
+  // (the last wavefronts first, so that a short A and a short B are not both
+  // on the first ones)
+  Share hb = share_panels(nw - 1 - wave, a.wavesN, ldb, wn_tag);
+  hb.dst += bbase;
+  const int cnt = ha.cnt + hb.cnt;
+  // Load j of a share: its uniform bytes from the stage's origin, and the
+  // bytes (0 or 64) that its rows' part of the XOR changes a lane's chunk by:
+  // bit 2 of its first row, where an instruction has fewer than 8 rows.
+  constexpr int CA = AK ? WM / 4 : CPR, CB = WN / 4;
+  constexpr bool kFlipA = AK ? flip_panel<I, CA>() && CA == 16 : CPR == 16;
+  constexpr bool kFlipB = flip_panel<I, CB>() && CB == 16;
+  auto at_a = [&](int j) __attribute__((always_inline)) {
+    const uint32_t s = static_cast<uint32_t>(ha.b0 + j * ha.db) << 6;
+    return ha.base + static_cast<uint64_t>(s / CA) * lda + (s % CA) * 16u;
+  };
+  auto at_b = [&](int j) __attribute__((always_inline)) {
+    const uint32_t s = static_cast<uint32_t>(hb.b0 + j * hb.db) << 6;
+    return hb.base + static_cast<uint64_t>(s / CB) * ldb + (s % CB) * 16u;
+  };
+  auto lane_a = [&](int j) __attribute__((always_inline)) {
+    const uint32_t r = (static_cast<uint32_t>(ha.b0 + j * ha.db) << 6) / CA;
+    return ha.row + (kFlipA ? ha.pos ^ ((r & 4) << 4) : ha.pos);
+  };
+  auto lane_b = [&](int j) __attribute__((always_inline)) {
+    const uint32_t r = (static_cast<uint32_t>(hb.b0 + j * hb.db) << 6) / CB;
+    return hb.row + (kFlipB ? hb.pos ^ ((r & 4) << 4) : hb.pos);
+  };
+  auto dst_a = [&](int j) { return ha.dst + static_cast<uint32_t>(ha.b0 + j * ha.db) * 1024u; };
+  auto dst_b = [&](int j) { return hb.dst + static_cast<uint32_t>(hb.b0 + j * hb.db) * 1024u; };
+
+  // All of this wavefront's loads of a stage, back to back, at any distance.
+  auto issue_all = [&](uint64_t ga, uint64_t gb, uint32_t slot) __attribute__((always_inline)) {
+    for (int j = 0; j < ha.cnt; ++j) dma_load16_if(1, 0, lane_a(j), ga + at_a(j), slot + dst_a(j));
+    for (int j = 0; j < hb.cnt; ++j) dma_load16_if(1, 0, lane_b(j), gb + at_b(j), slot + dst_b(j));
+  };
+
+  acc_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
+
+  // This lane's read offsets inside a slot. [k][n] panels: rows
+  // (cs·G + grp)·4 + q, column t·I + lane % I of the wavefront's panel.
+  const int grp = lane / I, l0 = lane % I;
+  auto panel_read = [&](int wi, int t, auto w) __attribute__((always_inline)) {
+    constexpr int W = decltype(w)::value;
+    int col = t * I + l0;
+    if constexpr (flip_panel<I, W / 4>()) col ^= (grp & 1) << 4;
+    return static_cast<uint32_t>(wi * (BK * W) + grp * 4 * W + col) * 4u;
+  };
+  uint32_t xa[TM], xb[TN];
+  const int af = fswz<CPR>(l0) ^ grp;  // I and the tile's rows are multiples of 16
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    if constexpr (AK)
+      xa[t] = panel_read(wm, t, std::integral_constant<int, WM>{});
+    else
+      xa[t] = static_cast<uint32_t>(wm * WM + t * I + l0) * (CPR * 16u);
+  }
+#pragma unroll
+  for (int t = 0; t < TN; ++t) xb[t] = bbase + panel_read(wn, t, std::integral_constant<int, WN>{});
+
+  f32x4 fa[2][TM], fb[2][TN];
+  auto load_frags = [&](const char* st, int cs, int fs) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      if constexpr (AK) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          fa[fs][t][q] = *reinterpret_cast<const float*>(st + xa[t] + (cs * G * 4 + q) * WM * 4);
+      } else {
+        fa[fs][t] = *reinterpret_cast<const f32x4*>(st + xa[t] + ((af ^ (cs * G)) << 4));
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        fb[fs][t][q] = *reinterpret_cast<const float*>(st + xb[t] + (cs * G * 4 + q) * WN * 4);
+  };
+  auto mfmas = [&](int fs, int q) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = mfma_f32(fa[fs][i][q], fb[fs][j][q], acc[i][j]);
+  };
+
+  const int kLoop = a.kLoop;
+  if (ns == 1) {
+    // a stage that leaves no room for a second one, or the only one
+    uint64_t ga = orgA, gb = orgB;
+    for (int l = 0; l < kLoop; ++l, ga += stepA, gb += stepB) {
+      issue_all(ga, gb, lds0);
+      waitcnt_vm<0>();
+      ring_barrier();
+      load_frags(smem, 0, 0);
+#pragma unroll
+      for (int cs = 0; cs < NCS; ++cs) {
+        if (cs + 1 < NCS) load_frags(smem, cs + 1, (cs + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mfmas(cs & 1, q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      waitcnt_lgkm0();
+      ring_barrier();
+    }
+  } else {
+    // Stage s goes into slot s mod ns. The boundary (wait for stage l + 1,
+    // barrier, its first fragments) comes before stage l's last chunk-step of
+    // MFMAs; the loads of stage l + ns, into the slot that every wavefront has
+    // read by then, are issued from that chunk-step on, over a window of NCS
+    // chunk-steps that ends before the next boundary.
+    const int npro = min(ns - 1, kLoop);
+    for (int l = 0; l < npro; ++l)
+      issue_all(orgA + l * stepA, orgB + l * stepB, lds0 + l * stage16);
+    const uint32_t ring = ns * stage16;
+
+    // NH: the loads of A, and of B, that a wavefront issues per stage, evenly
+    // spread over a window's 4·NCS MFMA groups as straight-line code; a
+    // wavefront with fewer (and every one after the last stage) issues the
+    // rest with no lane enabled, so the count is the same everywhere. With one
+    // wavefront a SIMD a branch in every group cost a fifth of the loop
+    // (1024³, 64×64×64 tiles: 20.8 µs per 1024 of K with branches, 16.9 µs
+    // without, 14 µs of MFMA). NH = 0: more loads than the offsets kept for
+    // them, or offsets past 32 bits: all at once after the boundary.
+    auto run = [&](auto nh) __attribute__((always_inline)) {
+      constexpr int NH = decltype(nh)::value;
+      uint32_t oa[NH ? NH : 1], ob[NH ? NH : 1];
+#pragma unroll
+      for (int i = 0; i < NH; ++i) {
+        oa[i] = lane_a(i) + static_cast<uint32_t>(at_a(i));
+        ob[i] = lane_b(i) + static_cast<uint32_t>(at_b(i));
+      }
+      struct Window {
+        uint64_t ga, gb;
+        uint32_t da, db;  // the next load's place in the slot
+        int na, nb;       // loads with their lanes enabled
+      };
+      const uint32_t sda = static_cast<uint32_t>(ha.db) * 1024u, sdb = static_cast<uint32_t>(hb.db) * 1024u;
+      auto window = [&](uint64_t ga, uint64_t gb, uint32_t slot, bool on) __attribute__((always_inline)) {
+        if (NH == 0 && on) issue_all(ga, gb, slot);
+        return Window{ga, gb, slot + dst_a(0), slot + dst_b(0), on ? ha.cnt : 0, on ? hb.cnt : 0};
+      };
+      // the loads that follow MFMA group u of a window
+      auto group = [&](Window& w, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+          if (2 * i * 4 * NCS / (2 * NH) == u) {
+            dma_load16_if(w.na, i, oa[i], w.ga, w.da);
+            w.da += sda;
+          }
+          if ((2 * i + 1) * 4 * NCS / (2 * NH) == u) {
+            dma_load16_if(w.nb, i, ob[i], w.gb, w.db);
+            w.db += sdb;
+          }
+        }
+      };
+      // stage l + 2 may still be on its way (ns = 3)
+      auto wait_stage = [&](int l) __attribute__((always_inline)) {
+        if (ns == 2)
+          waitcnt_vm<0>();
+        else if constexpr (NH > 0)
+          waitcnt_vm<2 * NH>();
+        else
+          wait_vm_at_most(__builtin_amdgcn_readfirstlane(l + 2 < kLoop ? cnt : 0));
+      };
+      // stage 0 has landed when at most the other npro − 1 are outstanding
+      wait_vm_at_most(__builtin_amdgcn_readfirstlane((npro - 1) * cnt));
+      ring_barrier();
+      Window w = window(orgA + static_cast<uint64_t>(ns - 1) * stepA,
+                        orgB + static_cast<uint64_t>(ns - 1) * stepB, lds0 + (ns - 1) * stage16,
+                        ns - 1 < kLoop);
+      load_frags(smem, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) group(w, q);
+      uint32_t cur_b = 0;  // this stage's slot, bytes from the ring's start
+      for (int l = 0; l < kLoop; ++l) {
+        const char* st = smem + cur_b;
+        const uint32_t nx_b = cur_b + stage16 == ring ? 0u : cur_b + stage16;
+#pragma unroll
+        for (int cs = 0; cs + 1 < NCS; ++cs) {
+          load_frags(st, cs + 1, (cs + 1) & 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            mfmas(cs & 1, q);
+            group(w, 4 + 4 * cs + q);
+          }
+        }
+        const bool more = l + 1 < kLoop;
+        // (outside the branch: past it the compiler would wait for the next
+        // stage's fragments too)
+        waitcnt_lgkm0();
+        if (more) {
+          wait_stage(l);
+          ring_barrier();
+          if constexpr (NCS >= 2) load_frags(smem + nx_b, 0, 0);
+        }
+        w = window(w.ga + stepA, w.gb + stepB, lds0 + cur_b, l + ns < kLoop);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          mfmas((NCS - 1) & 1, q);
+          group(w, q);
+        }
+        if constexpr (NCS == 1) {
+          if (more) load_frags(smem + nx_b, 0, 0);
+        }
+        cur_b = nx_b;
+      }
+    };
+    // The most loads of one operand that any wavefront of the workgroup has.
+    const int most = max(((BM << LGCPR) + 64 * nw - 1) / (64 * nw),
+                         ((BN << LGCPR) + 64 * nw - 1) / (64 * nw));
+    auto run_if = [&](auto nh) __attribute__((always_inline)) {
+      if constexpr (ring_needs<I, TM, TN, CPR>(decltype(nh)::value)) run(nh);
+    };
+    if (a.wide || most > 8)
+      run(std::integral_constant<int, 0>{});
+    else if (most > 4)
+      run_if(std::integral_constant<int, 8>{});
+    else if (most > 2)
+      run_if(std::integral_constant<int, 4>{});
+    else
+      run_if(std::integral_constant<int, 2>{});
+  }
+
+  store_tile<I, TM, TN>(a,
+                        a.C + (static_cast<int64_t>(gm) * BM + wm * WM) * a.N +
+                            (static_cast<int64_t>(gn) * BN + wn * WN),
+                        lane, acc);
+}
+
 // Launch bound: the largest wavefront count the legitimacy rule admits for
 // this accumulator size (acc + 96 ≤ 512 / ⌈waves/4⌉); the fast path is used
 // with at most 8 wavefronts.
@@ -1098,17 +1450,20 @@ template <int DT, int I, int TM, int TN, int CPR>
 __global__ void __launch_bounds__((launch_threads<I, TM, TN, CPR>())) gemm_kernel(KArgs a) {
   extern __shared__ u32x4 gt_smem[];
   char* smem = reinterpret_cast<char*>(gt_smem);
-  if constexpr (CPR > 0)
-    gemm_fast<DT, I, TM, TN, CPR>(a, smem);
-  else
+  if constexpr (CPR == 0)
     gemm_generic<DT, I, TM, TN>(a, smem);
+  else if constexpr (DT == 0)
+    gemm_ring_f32<I, TM, TN, CPR, false>(a, smem);
+  else
+    gemm_fast<I, TM, TN, CPR>(a, smem);
 }
 
-// Register-staged fast path for a K-major A.
+// fp32 fast path for a K-major A.
 template <int DT, int I, int TM, int TN, int CPR>
 __global__ void __launch_bounds__((launch_threads<I, TM, TN, CPR>())) gemm_kernel_akm(KArgs a) {
+  static_assert(DT == 0, "the K-major-A fast path is fp32 only");
   extern __shared__ u32x4 gt_smem[];
-  gemm_fast<DT, I, TM, TN, CPR, true>(a, reinterpret_cast<char*>(gt_smem));
+  gemm_ring_f32<I, TM, TN, CPR, true>(a, reinterpret_cast<char*>(gt_smem));
 }
 
 // bf16 fast path with direct global→LDS loads: a kernel of its own, so that

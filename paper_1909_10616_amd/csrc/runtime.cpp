@@ -34,6 +34,25 @@ int hip_fail(hipError_t e, const char* what) {
   return GT_EHIP;
 }
 
+// Ring stages of the fp32 fast path: 3, or 2 (1 where no second stage fits or K
+// has only one), so that as many workgroups share a compute unit as the grid
+// has for each, up to 4 and to what their registers allow: a workgroup that
+// shares its CU hides its stage boundaries and its C stores behind another's
+// MFMAs, which is worth more than a third stage. Measured: 4032×960×384 in
+// 945 tiles of 64×64×32, 2 wavefronts: 44.7 µs with 3 stages and 3 workgroups
+// a CU, 34.0 µs with 2 stages and 4; 2048³ in 512 tiles of 64×128×32: 213 µs
+// with 6 stages and 1 workgroup, 157 µs with 3 stages and 2. A fourth and
+// fifth stage changed nothing (1024³, one 64×64×64 tile a CU: 27.9, 27.8 and
+// 28.3 µs with 3, 4 and 5).
+int64_t f32_ring_stages(const Levels& L, int64_t stage_bytes) {
+  const int64_t groups = L.gridM * L.gridN * L.kSplit;
+  const int64_t by_regs = std::max<int64_t>(1, 4 * (512 / (L.acc + 96)) / L.W);
+  int64_t share = std::min<int64_t>({(groups + 255) / 256, by_regs, int64_t{4}});
+  while (share > 1 && kLdsMax / share / stage_bytes < 2) --share;
+  return std::max<int64_t>(
+      1, std::min<int64_t>({kLdsMax / share / stage_bytes, L.kLoop, int64_t{3}}));
+}
+
 }  // namespace
 
 int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const void* A,
@@ -66,11 +85,14 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   const int G = 64 / L.I;
   const int64_t cpr = L.BK / vec;  // 16-byte chunks per LDS row
   const bool cpr_ok = L.BK % vec == 0 && (cpr == 2 || cpr == 4 || cpr == 8 || cpr == 16);
-  // (a K-major A needs 16-byte m chunks, M % vec; its fast path is fp32 only)
+  // (a K-major A needs 16-byte m chunks, M % vec; its fast path is fp32 only;
+  // the fp32 ring's loads keep 32-bit offsets over the up to 32 rows of one
+  // instruction)
   const bool fast = L.blkM % L.I == 0 && L.blkN % L.I == 0 && L.kBlk % L.IK == 0 &&
                     L.BK % (vec * G) == 0 && cpr_ok && L.BN % vec == 0 && K % vec == 0 &&
                     N % vec == 0 && L.W <= 8 && aligned16(A) && aligned16(B) &&
-                    (!akm || (dt == GT_F32 && L.BM % vec == 0 && M % vec == 0));
+                    (!akm || (dt == GT_F32 && L.BM % vec == 0 && M % vec == 0)) &&
+                    (dt == GT_BF16 || std::max({akm ? M : K, N}) < (int64_t{1} << 25));
   const int64_t stage_bytes = (L.BM * L.BK + L.BK * L.BN) * L.elem;
   const bool dbuf = L.kLoop >= 2 && 2 * stage_bytes <= kLdsMax;
   // bf16 fast path with direct global->LDS loads into a ring of ns stages:
@@ -79,10 +101,12 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   // element offsets
   const int64_t achunks = L.BM * L.BK / 8, bchunks = L.BK * L.BN / 8;
   const int64_t dl_inst = (achunks + bchunks) / 64;
-  const int64_t ns = std::min<int64_t>(8, kLdsMax / std::max<int64_t>(stage_bytes, 1));
+  const int64_t ns_dl = std::min<int64_t>(8, kLdsMax / std::max<int64_t>(stage_bytes, 1));
   const bool dl = fast && dt == GT_BF16 && !akm && achunks % (64 * L.W) == 0 &&
-                  bchunks % (64 * L.W) == 0 && dl_inst / L.W <= dl_inst_cap(L.acc) && ns >= 2 &&
+                  bchunks % (64 * L.W) == 0 && dl_inst / L.W <= dl_inst_cap(L.acc) && ns_dl >= 2 &&
                   L.BM * K < (int64_t{1} << 31) && L.BK * N < (int64_t{1} << 31);
+  const bool ring = dl || (fast && dt == GT_F32);
+  const int64_t ns = dl ? ns_dl : (ring ? f32_ring_stages(L, stage_bytes) : 0);
 
   KArgs& a = out->args;
   std::memset(&a, 0, sizeof(a));
@@ -122,11 +146,13 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   a.lgBM = ilog2(L.BM);
   a.bVec = (L.BN % vec == 0 && N % vec == 0 && aligned16(B)) ? vec : 1;
   a.dl = dl ? 1 : 0;
-  a.ns = dl ? static_cast<int32_t>(ns) : 0;
+  a.ns = static_cast<int32_t>(ns);
+  // bytes from a stage's origins to its last row of A (row-major) or k row
+  a.wide = std::max({akm ? L.BK * M : L.BM * K, L.BK * N}) >= (int64_t{1} << 30) ? 1 : 0;
 
   out->grid = dim3(static_cast<unsigned>(L.gridM * L.gridN), static_cast<unsigned>(L.kSplit), 1);
   out->block = dim3(static_cast<unsigned>(64 * L.W), 1, 1);
-  out->lds = static_cast<size_t>(stage_bytes * (dl ? ns : (dbuf ? 2 : 1)));
+  out->lds = static_cast<size_t>(stage_bytes * (ring ? ns : (dbuf ? 2 : 1)));
   out->fast = fast;
   out->fn = find_gemm_kernel(dt, L.I, fast ? static_cast<int>(cpr) : 0,
                              static_cast<int>(L.TM), static_cast<int>(L.TN), fast && akm);
