@@ -7,9 +7,11 @@
 //   k index = ((kLoop·kSplit + z)·kSub + s)·kBlk + b
 // Compile-time parameters: input dtype, MFMA size I (16/32), MFMA tiles per
 // wavefront TM × TN, and the path:
-//   generic — any legitimate configuration; blocks smaller than the MFMA
-//             instruction are zero-padded in registers, LDS holds the natural
-//             row-major tiles;
+//   generic — any legitimate configuration: wavefronts that read their own
+//             operands (gemm_stream), or, where blocks, alignment or LDS do not
+//             allow that, stages shared through LDS in the natural row-major
+//             layout, blocks smaller than the MFMA instruction zero-padded in
+//             registers (gemm_generic);
 //   fast    — blocks that are multiples of the instruction, direct
 //             global→LDS loads into a ring of stages: bf16 (gemm_fast_dl) and
 //             fp32 (gemm_ring_f32). bf16 tiles the ring cannot serve stage
@@ -48,6 +50,7 @@ struct KArgs {
   int32_t ns;              // ring stages (direct-load path)
   int32_t aKM;             // A given K-major (K×M row-major, element (m, k) at A[k·M + m])
   int32_t lgBM;
+  int32_t stream;          // generic path: wavefronts read their own operands
   int32_t wide;            // fp32 ring: a stage's offsets from its origins exceed 32 bits
 };
 
@@ -1431,6 +1434,276 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
                         lane, acc);
 }
 
+// ---------------------------------------------------------------------------
+// Generic path without shared stages ("stream"): every wavefront reads its own
+// operands, so there are no barriers, and a K step takes IK consecutive k
+// whatever kBlk and the stage depth are (the K levels only say where a slice's
+// stages lie: one run of all K, or runs of BK with a K split).
+//   fp32: 16-byte (row-major A) and 4-byte loads straight into MFMA operands;
+//   bf16: a row-major A is loaded the same way, 8 k a lane; B, and a K-major A,
+//   pass through a piece of LDS of the wavefront's own, written 16 bytes a
+//   lane and read back with the transposing read (chunks of row k XOR-ed by
+//   bswz(k)). LDS operations of a wavefront complete in order, so one buffer
+//   serves every step.
+// Loads run PF steps ahead in registers. Rows and columns that a block smaller
+// than I lacks read the block's last ones; their products are not stored. Past
+// the end of K both operands are zero.
+// Bound by the loads themselves (each wavefront fetches (WM + WN)·K elements
+// through its CU's L1) where blocks are small. Against the shared stages of
+// gemm_generic, which gather bf16 operands from LDS 2 bytes at a time, pad
+// every sub-step to the instruction's K and cross two barriers a stage:
+// 1360×1200×720 bf16 in 16×16 tiles 131 -> 33 µs, 2048³ bf16 with a K-major A
+// in 128×128 tiles 224 -> 38 µs, 1440×968×176 fp32 in 32×8 tiles 32 -> 21 µs.
+template <int TM, int TN>
+constexpr bool has_stream() {
+  return TM + TN <= 10;
+}
+
+template <int DT, int I, int TM, int TN, bool AK>
+__device__ __forceinline__ void gemm_stream(const KArgs& a, char* smem) {
+  using T = typename Elem<DT>::T;
+  using acc_t = typename AccT<I>::type;
+  constexpr int NACC = AccT<I>::N;
+  constexpr int G = 64 / I;
+  constexpr int SZ = sizeof(T);
+  constexpr int KL = 16 / SZ;  // consecutive k a lane holds of a step: 8 bf16, 4 fp32
+  constexpr int KS = KL * G;   // k per step
+  constexpr int PF = TM + TN <= 4 ? 4 : 2;  // steps of loads in flight (even)
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int wm = wave % a.wavesM;
+  const int wn = wave / a.wavesM;
+  int gm, gn;
+  tile_of(a, gm, gn);
+  const int z = blockIdx.y;
+  const int grp = lane / I, l0 = lane % I;
+  const int tpbM = 1 << a.lgTpbM, tpbN = 1 << a.lgTpbN;
+  const int64_t row0 = static_cast<int64_t>(gm) * a.BM + wm * a.WM;
+  const int64_t col0 = static_cast<int64_t>(gn) * a.BN + wn * a.WN;
+  const int64_t k0 = static_cast<int64_t>(z) * a.BK;
+  const int64_t lda = AK ? a.M : a.K;
+  const char* pa = reinterpret_cast<const char*>(a.A) + (AK ? k0 * lda + row0 : row0 * lda + k0) * SZ;
+  const char* pb = reinterpret_cast<const char*>(a.B) + (k0 * a.N + col0) * SZ;
+  const int64_t stepa = (AK ? lda : 1) * KS * SZ, stepb = a.N * KS * SZ;
+  // steps of this slice: runs of `run` k, `skip` k apart
+  const int64_t run = a.kSplit == 1 ? a.K : a.BK;
+  const int64_t skip = a.kSplit == 1 ? 0 : static_cast<int64_t>(a.kSplit - 1) * a.BK;
+  const int64_t skipa = skip * (AK ? lda : 1) * SZ, skipb = skip * a.N * SZ;
+  const int per_run = static_cast<int>(run / KS);
+  const int full = per_run * (a.kSplit == 1 ? 1 : a.kLoop);
+  const int left = static_cast<int>(run - static_cast<int64_t>(per_run) * KS);  // kSplit 1 only
+
+  // Row (column) of the wavefront's tile that MFMA tile t has at in-tile row l.
+  auto row_of = [&](int t, int l) {
+    return (t >> a.lgTpbM) * a.blkM + min((t & (tpbM - 1)) * I + l, a.blkM - 1);
+  };
+  auto col_of = [&](int t, int l) {
+    return (t >> a.lgTpbN) * a.blkN + min((t & (tpbN - 1)) * I + l, a.blkN - 1);
+  };
+
+  // One operand given with K as its rows ([k][x], x contiguous, ld long).
+  // bf16: TX loads of 64 chunks cover the KS × width panel; fp32: 4 rows a lane.
+  struct Panel {
+    uint32_t off[8];    // bytes from the step's origin of the lane's loads
+    uint32_t put[8];    // bf16: where they go in the wavefront's LDS
+    uint32_t get[8];    // bf16: this lane's transposing reads (first of two)
+    int row[8];         // first k row of each load, for the end of K
+  };
+  auto panel = [&](Panel& p, auto txt, int64_t ld, int width, char* lds, auto xof) __attribute__((always_inline)) {
+    constexpr int TX = decltype(txt)::value;
+    if constexpr (DT == 1) {
+      const int cw = width >> 3;  // a power of two
+      const int lgcw = 31 - __builtin_clz(cw);
+      const int i16 = lane & 15, g16 = lane >> 4;
+      const int kgrp = I == 32 ? (g16 >> 1) : g16;
+      const int ncol = (I == 32 ? 16 * (g16 & 1) : 0) + 4 * (i16 & 3);
+#pragma unroll
+      for (int t = 0; t < TX; ++t) {
+        const int c = min(lane + 64 * t, KS * cw - 1);
+        const int k = c >> lgcw, x = c & (cw - 1);
+        p.row[t] = k;
+        p.off[t] = (static_cast<uint32_t>(k) * static_cast<uint32_t>(ld) + static_cast<uint32_t>(x * 8)) * 2u;
+        p.put[t] = lds_off(lds) + static_cast<uint32_t>((k << lgcw) + (x ^ bswz(k, cw))) * 16u;
+        const int kr = kgrp * 8 + (i16 >> 2);
+        const int col = min(xof(t, 0) + ncol, width - 4);
+        // the second read is 4 rows on: bswz depends on k mod 4 and bit 3 only
+        p.get[t] = lds_off(lds) + static_cast<uint32_t>((kr << lgcw) + ((col >> 3) ^ bswz(kr, cw))) * 16u +
+                   static_cast<uint32_t>(col & 4) * 2u;
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < TX; ++t) {
+        p.row[t] = grp * 4;
+        p.off[t] = (static_cast<uint32_t>(grp * 4) * static_cast<uint32_t>(ld) +
+                    static_cast<uint32_t>(xof(t, l0))) * 4u;
+      }
+    }
+  };
+  Panel fb, fa;
+  const uint32_t ldb4 = static_cast<uint32_t>(a.N) * 4u, lda4 = static_cast<uint32_t>(lda) * 4u;
+  // the wavefront's piece of LDS, for its B panel and then for its A panel
+  char* const mine = smem + wave * (KS * (AK ? max(a.WM, a.WN) : a.WN) * 2);
+  panel(fb, std::integral_constant<int, TN>{}, a.N, a.WN, mine, col_of);
+  const int bgap = (a.WN >> 3) * 64, agap = (a.WM >> 3) * 64;  // bytes between a fragment's two reads
+  if constexpr (AK) {
+    panel(fa, std::integral_constant<int, TM>{}, lda, a.WM, mine, row_of);
+  } else {
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+      fa.off[t] = (static_cast<uint32_t>(row_of(t, l0)) * static_cast<uint32_t>(lda) +
+                   static_cast<uint32_t>(grp * KL)) * static_cast<uint32_t>(SZ);
+  }
+
+  acc_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
+
+  u32x4 ra[PF][TM], rb[PF][TN];
+  // kv: k of this step that exist, KS inside K (`end` false)
+  auto load_panel = [&](u32x4& v, const char* base, const Panel& p, int t, uint32_t ld4, int kv,
+                        auto end) __attribute__((always_inline)) {
+    if constexpr (DT == 1) {
+      const bool in = !decltype(end)::value || p.row[t] < kv;
+      v = *reinterpret_cast<const u32x4*>(base + (in ? p.off[t] : 0u));
+      if (!in) v = u32x4{0, 0, 0, 0};
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const bool in = !decltype(end)::value || p.row[t] + q < kv;
+        const unsigned x = *reinterpret_cast<const unsigned*>(base + (in ? p.off[t] + q * ld4 : 0u));
+        v[q] = in ? x : 0u;
+      }
+    }
+  };
+  auto load = [&](int s, int kv, auto end) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      if constexpr (AK) {
+        load_panel(ra[s][t], pa, fa, t, lda4, kv, end);
+      } else {
+        const bool in = !decltype(end)::value || grp * KL < kv;  // K is a multiple of KL here
+        ra[s][t] = *reinterpret_cast<const u32x4*>(pa + (in ? fa.off[t] : 0u));
+        if (!in) ra[s][t] = u32x4{0, 0, 0, 0};
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < TN; ++t) load_panel(rb[s][t], pb, fb, t, ldb4, kv, end);
+  };
+  int in_run = 0;
+  auto advance = [&]() __attribute__((always_inline)) {
+    pa += stepa;
+    pb += stepb;
+    // (a select, not a branch, between the loads)
+    const bool over = ++in_run == per_run;
+    in_run = over ? 0 : in_run;
+    pa += over ? skipa : 0;
+    pb += over ? skipb : 0;
+  };
+  typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  auto fetch = [&](u32x4& v, const Panel& p, int t, int gap) __attribute__((always_inline)) {
+    s16x4 h[2];
+    h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(p.get[t]));
+    h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(p.get[t] + gap));
+    v = __builtin_bit_cast(u32x4, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  // bf16: a loaded step's panels through LDS into MFMA operands (f = 0 or 1)
+  u32x4 af[2][TM], bf[2][TN];
+  auto transpose = [&](int s, int f) __attribute__((always_inline)) {
+    if constexpr (DT == 1) {
+#pragma unroll
+      for (int t = 0; t < TN; ++t) *(lds_u32x4*)(uintptr_t)(fb.put[t]) = rb[s][t];
+#pragma unroll
+      for (int t = 0; t < TN; ++t) fetch(bf[f][t], fb, t, bgap);
+      if constexpr (AK) {
+#pragma unroll
+        for (int t = 0; t < TM; ++t) *(lds_u32x4*)(uintptr_t)(fa.put[t]) = ra[s][t];
+#pragma unroll
+        for (int t = 0; t < TM; ++t) fetch(af[f][t], fa, t, agap);
+      }
+    }
+  };
+  auto multiply = [&](int s, int f) __attribute__((always_inline)) {
+    if constexpr (DT == 1) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = mfma_bf16(__builtin_bit_cast(bf16x8, AK ? af[f][i] : ra[s][i]),
+                                __builtin_bit_cast(bf16x8, bf[f][j]), acc[i][j]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = mfma_f32(__builtin_bit_cast(f32x4, ra[s][i])[q],
+                                 __builtin_bit_cast(f32x4, rb[s][j])[q], acc[i][j]);
+    }
+  };
+
+  int issued = 0, done = 0;
+#pragma unroll
+  for (int s = 0; s < PF; ++s)
+    if (issued < full) {
+      load(s, KS, std::false_type{});
+      advance();
+      ++issued;
+    }
+  if (full) transpose(0, 0);
+  // Step `done` is in slot s; the next one's panels pass through LDS while its
+  // MFMAs run, then its slot is loaded again. Without a branch between them
+  // the compiler counts the loads in flight and waits for the one it needs;
+  // the last steps check what is left.
+  for (; done + 2 * PF <= full; done += PF) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s) {
+      transpose((s + 1) % PF, (s + 1) & 1);
+      multiply(s, s & 1);
+      load(s, KS, std::false_type{});
+      advance();
+    }
+    issued += PF;
+  }
+  while (done < full) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s)
+      if (done < full) {
+        ++done;
+        if (done < full) transpose((s + 1) % PF, (s + 1) & 1);
+        multiply(s, s & 1);
+        if (issued < full) {
+          load(s, KS, std::false_type{});
+          advance();
+          ++issued;
+        }
+      }
+  }
+  if (left) {
+    load(0, left, std::true_type{});
+    transpose(0, 0);
+    multiply(0, 0);
+  }
+
+  float* Cw = a.C + row0 * a.N + col0;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int e = 0; e < NACC; ++e) {
+      const int ri = (i & (tpbM - 1)) * I + out_row<I>(lane, e);
+      float* const p = Cw + static_cast<int64_t>((i >> a.lgTpbM) * a.blkM + ri) * a.N;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int ci = (j & (tpbN - 1)) * I + l0;
+        if (ri < a.blkM && ci < a.blkN)
+          put(a.atomic != 0, p + (j >> a.lgTpbN) * a.blkN + ci, acc[i][j][e]);
+      }
+    }
+}
+
 // Launch bound: the largest wavefront count the legitimacy rule admits for
 // this accumulator size (acc + 96 ≤ 512 / ⌈waves/4⌉); the fast path is used
 // with at most 8 wavefronts.
@@ -1450,12 +1723,20 @@ template <int DT, int I, int TM, int TN, int CPR>
 __global__ void __launch_bounds__((launch_threads<I, TM, TN, CPR>())) gemm_kernel(KArgs a) {
   extern __shared__ u32x4 gt_smem[];
   char* smem = reinterpret_cast<char*>(gt_smem);
-  if constexpr (CPR == 0)
+  if constexpr (CPR == 0) {
     gemm_generic<DT, I, TM, TN>(a, smem);
-  else if constexpr (DT == 0)
+  } else if constexpr (DT == 0) {
     gemm_ring_f32<I, TM, TN, CPR, false>(a, smem);
-  else
+  } else {
     gemm_fast<I, TM, TN, CPR>(a, smem);
+  }
+}
+
+// Generic path whose wavefronts read their own operands, at most 8 of them.
+template <int DT, int I, int TM, int TN, bool AK>
+__global__ void __launch_bounds__((launch_threads<I, TM, TN, 1>())) gemm_kernel_stream(KArgs a) {
+  extern __shared__ u32x4 gt_smem[];
+  gemm_stream<DT, I, TM, TN, AK>(a, reinterpret_cast<char*>(gt_smem));
 }
 
 // fp32 fast path for a K-major A.
@@ -1509,6 +1790,13 @@ hipError_t launch_gemm(const KArgs& a, dim3 grid, dim3 block, size_t lds, hipStr
       if (a.dl) {
         static std::atomic<uint64_t> attr_dl{0};
         return launch_one(gemm_kernel_dl<I, TM, TN, CPR>, attr_dl, a, grid, block, lds, s);
+      }
+    }
+    if constexpr (CPR == 0 && has_stream<TM, TN>()) {
+      if (a.stream) {
+        static std::atomic<uint64_t> attr_s{0}, attr_sk{0};
+        return a.aKM ? launch_one(gemm_kernel_stream<DT, I, TM, TN, true>, attr_sk, a, grid, block, lds, s)
+                     : launch_one(gemm_kernel_stream<DT, I, TM, TN, false>, attr_s, a, grid, block, lds, s);
       }
     }
     static std::atomic<uint64_t> attr{0};

@@ -53,6 +53,24 @@ int64_t f32_ring_stages(const Levels& L, int64_t stage_bytes) {
       1, std::min<int64_t>({kLdsMax / share / stage_bytes, L.kLoop, int64_t{3}}));
 }
 
+// Whether the generic path's wavefronts can read their own operands: steps of
+// KS consecutive k inside every run of them, 16-byte loads on 16-byte
+// boundaries (bf16: of rows of A or of [k][x] panels whose blocks are whole
+// groups of 4 columns; fp32: of row-major A only), 32-bit offsets, at most 8
+// wavefronts, and for bf16 a piece of the launch's LDS for every wavefront's panels.
+bool stream_serves(const Levels& L, int64_t M, int64_t N, int64_t K, int dt, bool akm, bool a16,
+                   bool b16, int64_t lds_bytes) {
+  const int64_t KL = dt == GT_BF16 ? 8 : 4, KS = KL * (64 / L.I);
+  const int64_t WM = L.repM * L.blkM, WN = L.repN * L.blkN;
+  if (L.W > 8 || L.TM + L.TN > 10 || (L.kSplit > 1 && L.BK % KS != 0) || K >= (int64_t{1} << 31)) return false;
+  if (std::max(akm ? KS * M : WM * K, KS * N) * L.elem >= (int64_t{1} << 32)) return false;
+  if (!akm && (K % KL != 0 || !a16)) return false;
+  if (dt == GT_F32) return true;
+  if (WN % 8 != 0 || N % 8 != 0 || L.blkN % 4 != 0 || !b16) return false;
+  if (akm && (WM % 8 != 0 || M % 8 != 0 || L.blkM % 4 != 0 || !a16)) return false;
+  return L.W * KS * (akm ? std::max(WM, WN) : WN) * 2 <= lds_bytes;
+}
+
 }  // namespace
 
 int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const void* A,
@@ -149,6 +167,11 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   a.ns = static_cast<int32_t>(ns);
   // bytes from a stage's origins to its last row of A (row-major) or k row
   a.wide = std::max({akm ? L.BK * M : L.BM * K, L.BK * N}) >= (int64_t{1} << 30) ? 1 : 0;
+
+  a.stream = !fast && stream_serves(L, M, N, K, dt, akm, aligned16(A), aligned16(B),
+                                    stage_bytes * (dbuf ? 2 : 1))
+                 ? 1
+                 : 0;
 
   out->grid = dim3(static_cast<unsigned>(L.gridM * L.gridN), static_cast<unsigned>(L.kSplit), 1);
   out->block = dim3(static_cast<unsigned>(64 * L.W), 1, 1);
