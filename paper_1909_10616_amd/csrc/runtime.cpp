@@ -34,23 +34,32 @@ int hip_fail(hipError_t e, const char* what) {
   return GT_EHIP;
 }
 
-// Ring stages of the fp32 fast path: 3, or 2 (1 where no second stage fits or K
-// has only one), so that as many workgroups share a compute unit as the grid
-// has for each, up to 4 and to what their registers allow: a workgroup that
-// shares its CU hides its stage boundaries and its C stores behind another's
-// MFMAs, which is worth more than a third stage. Measured: 4032×960×384 in
-// 945 tiles of 64×64×32, 2 wavefronts: 44.7 µs with 3 stages and 3 workgroups
-// a CU, 34.0 µs with 2 stages and 4; 2048³ in 512 tiles of 64×128×32: 213 µs
-// with 6 stages and 1 workgroup, 157 µs with 3 stages and 2. A fourth and
-// fifth stage changed nothing (1024³, one 64×64×64 tile a CU: 27.9, 27.8 and
-// 28.3 µs with 3, 4 and 5).
-int64_t f32_ring_stages(const Levels& L, int64_t stage_bytes) {
+// LDS bytes of a ring whose workgroups share their compute unit: the whole, a
+// half, a third or a quarter of it, as many parts as the grid has workgroups
+// for each CU and their registers allow, while a part holds min_stages. A
+// workgroup that shares its CU hides its stage boundaries and its C stores
+// behind another's MFMAs; one that takes all of LDS for a deeper ring runs
+// alone, and its grid in rounds. Measured with the most stages that fit and one
+// workgroup a CU against 2 to 4 of them: fp32 4032×960×384 in 945 tiles of
+// 64×64×32 90 -> 34 µs, 2048³ in 512 tiles of 64×128×32 213 -> 157 µs; bf16
+// 2944×1024×4096 in 736 tiles of 64×64×32 91 -> 54 µs, 512×1344×960 in 336
+// tiles of 64×32×64 20.0 -> 13.4 µs.
+int64_t ring_share_bytes(const Levels& L, int64_t stage_bytes, int64_t min_stages) {
   const int64_t groups = L.gridM * L.gridN * L.kSplit;
   const int64_t by_regs = std::max<int64_t>(1, 4 * (512 / (L.acc + 96)) / L.W);
   int64_t share = std::min<int64_t>({(groups + 255) / 256, by_regs, int64_t{4}});
-  while (share > 1 && kLdsMax / share / stage_bytes < 2) --share;
-  return std::max<int64_t>(
-      1, std::min<int64_t>({kLdsMax / share / stage_bytes, L.kLoop, int64_t{3}}));
+  while (share > 1 && kLdsMax / share / stage_bytes < min_stages) --share;
+  return kLdsMax / share;
+}
+
+// Ring stages of the fp32 fast path: at most 3 (a fourth and fifth changed
+// nothing: 1024³, one 64×64×64 tile a CU, 27.9, 27.8 and 28.3 µs with 3, 4
+// and 5), 2 where that lets another workgroup in (the 945 tiles above: 44.7 µs
+// with 3 stages and 3 workgroups, 34.0 µs with 2 and 4), 1 where no second
+// fits or K has only one.
+int64_t f32_ring_stages(const Levels& L, int64_t stage_bytes) {
+  return std::max<int64_t>(1, std::min<int64_t>({ring_share_bytes(L, stage_bytes, 2) / stage_bytes,
+                                                 L.kLoop, int64_t{3}}));
 }
 
 // Whether the generic path's wavefronts can read their own operands: steps of
@@ -119,7 +128,7 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   // element offsets
   const int64_t achunks = L.BM * L.BK / 8, bchunks = L.BK * L.BN / 8;
   const int64_t dl_inst = (achunks + bchunks) / 64;
-  const int64_t ns_dl = std::min<int64_t>(8, kLdsMax / std::max<int64_t>(stage_bytes, 1));
+  const int64_t ns_dl = std::min<int64_t>(8, ring_share_bytes(L, stage_bytes, 3) / stage_bytes);
   const bool dl = fast && dt == GT_BF16 && !akm && achunks % (64 * L.W) == 0 &&
                   bchunks % (64 * L.W) == 0 && dl_inst / L.W <= dl_inst_cap(L.acc) && ns_dl >= 2 &&
                   L.BM * K < (int64_t{1} << 31) && L.BK * N < (int64_t{1} << 31);
