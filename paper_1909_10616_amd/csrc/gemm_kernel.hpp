@@ -13,11 +13,9 @@
 //             layout, blocks smaller than the MFMA instruction zero-padded in
 //             registers (gemm_generic);
 //   fast    — blocks that are multiples of the instruction, direct
-//             global→LDS loads into a ring of stages: bf16 (gemm_fast_dl) and
-//             fp32 (gemm_ring_f32). bf16 tiles the ring cannot serve stage
-//             16-byte loads through registers one stage ahead (gemm_fast), B
-//             transposed there so every LDS fragment read is 16 bytes, LDS
-//             tiles XOR-swizzled by 128-byte line to avoid bank conflicts.
+//             global→LDS loads into a ring of stages: gemm_fast_dl for bf16
+//             stages whose loads divide evenly over the wavefronts into the
+//             counts it is built for, gemm_ring for all others and for fp32.
 // Everything else (grid, waves, block extents, stage depth, split-K, double
 // buffering) is a runtime argument.
 #pragma once
@@ -46,12 +44,13 @@ struct KArgs {
   int32_t atomic;          // split-K: accumulate with fp32 atomics
   int32_t remap;           // XCD-aware workgroup order
   int32_t aVec, bVec;      // generic path: 1 or 16-byte vector tile loads
-  int32_t dl;              // fast path: direct global->LDS loads into a ring
-  int32_t ns;              // ring stages (direct-load path)
+  int32_t dl;              // bf16 fast path: loads in whole equal shares (gemm_fast_dl's shape)
+  int32_t dlk;             // … that gemm_fast_dl itself takes
+  int32_t ns;              // ring stages (fast path)
   int32_t aKM;             // A given K-major (K×M row-major, element (m, k) at A[k·M + m])
   int32_t lgBM;
   int32_t stream;          // generic path: wavefronts read their own operands
-  int32_t wide;            // fp32 ring: a stage's offsets from its origins exceed 32 bits
+  int32_t wide;            // gemm_ring: a stage's offsets from its origins exceed 32 bits
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -339,267 +338,14 @@ __device__ void gemm_generic(const KArgs& a, char* smem) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Register-staged fast path (bf16)
-// ---------------------------------------------------------------------------
-
 // 16-byte chunk q of a tile → its LDS slot: XOR inside each 128-byte line
 // (8 chunks) with a hash of the line index, so that the 8 or 16 lanes served
 // together by a 16-byte LDS read hit distinct banks.
 __device__ __forceinline__ int swz(int q) { return q ^ (((q >> 3) ^ (q >> 6)) & 7); }
 
-constexpr int kPfA = 8;  // A chunks staged in registers per thread
-constexpr int kPfB = 1;  // B VEC×VEC blocks staged per thread
-
-// Transpose an 8×8 block of 16-bit values held as row chunks into column
-// chunks; dword w of a chunk holds elements 2w (low), 2w+1 (high).
-__device__ __forceinline__ void transpose_block(const u32x4* in, u32x4* out) {
-  const uint32_t* r = reinterpret_cast<const uint32_t*>(in);  // r[j*4 + w]
-  uint32_t* o = reinterpret_cast<uint32_t*>(out);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t lo = r[(2 * w) * 4 + u], hi = r[(2 * w + 1) * 4 + u];
-      o[(2 * u) * 4 + w] = (lo & 0xffffu) | (hi << 16);
-      o[(2 * u + 1) * 4 + w] = (lo >> 16) | (hi & 0xffff0000u);
-    }
-  }
-}
-
 template <int V>
 constexpr int ilog2c() {
   return V <= 1 ? 0 : 1 + ilog2c<V / 2>();
-}
-
-// CPR = 16-byte chunks per LDS row = BK / VEC, a compile-time constant so
-// that the chunk-step loop unrolls: the fragments of chunk-step cs+1 are read
-// from LDS while the MFMAs of chunk-step cs run.
-template <int I, int TM, int TN, int CPR>
-__device__ void gemm_fast(const KArgs& a, char* smem) {
-  using T = Elem<1>::T;
-  using acc_t = typename AccT<I>::type;
-  constexpr int NACC = AccT<I>::N;
-  constexpr int VEC = Elem<1>::VEC;
-  constexpr int LGV = 3;
-  constexpr int G = 64 / I;          // lane groups of an MFMA operand
-  constexpr int NCS = CPR / G;       // chunk-steps per stage
-  constexpr int LGCPR = ilog2c<CPR>();
-  constexpr int NLINE = CPR >= 8 ? CPR / 8 : 1;  // 128-byte lines per LDS row
-  static_assert(NCS >= 1, "stage shallower than one MFMA K step");
-  const int tid = threadIdx.x;
-  const int nthr = blockDim.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % a.wavesM;
-  const int wn = wave / a.wavesM;
-  int gm, gn;
-  tile_of(a, gm, gn);
-  const int z = blockIdx.y;
-
-  const int achunks = a.BM << LGCPR;
-  const int lgnbn = a.lgBN - LGV;    // B blocks along n = BN / VEC
-  const int bblocks = CPR << lgnbn;  // CPR blocks along k
-  const int stage = achunks + (a.BN << LGCPR);  // chunks per stage
-  u32x4* lds = reinterpret_cast<u32x4*>(smem);
-
-  const T* Ag = reinterpret_cast<const T*>(a.A) + static_cast<int64_t>(gm) * a.BM * a.K;
-  const T* Bg = reinterpret_cast<const T*>(a.B) + static_cast<int64_t>(gn) * a.BN;
-
-  const int rounds = max((achunks + nthr * kPfA - 1) / (nthr * kPfA),
-                         (bblocks + nthr * kPfB - 1) / (nthr * kPfB));
-  const bool prefetch = rounds == 1;
-
-  // This thread's chunks: A chunk i is e_i = ta + i·nthr with ta = tid, i.e.
-  // row (ta >> LGCPR) + i·(nthr >> LGCPR), column chunk ta & (CPR − 1), so
-  // one base offset and a uniform row stride address all of them. Tile and
-  // thread counts are powers of two: either every thread owns na chunks, or
-  // the tile has fewer chunks than threads, na = 1 and the surplus threads
-  // take the last chunk (ta clamped) and later write those same bytes to
-  // its slot. The loads therefore sit under wavefront-uniform conditions only.
-  const int na = __builtin_amdgcn_readfirstlane(min(kPfA, (achunks + nthr - 1) / nthr));
-  const int nbb = __builtin_amdgcn_readfirstlane(min(kPfB, (bblocks + nthr - 1) / nthr));
-  const int ta = min(tid, achunks - 1);
-  const int64_t aoff0 = static_cast<int64_t>(ta >> LGCPR) * a.K + ((ta & (CPR - 1)) << LGV);
-  const int64_t astride = static_cast<int64_t>(nthr >> LGCPR) * a.K;
-  int64_t boff[kPfB];
-  int bq0[kPfB];
-#pragma unroll
-  for (int i = 0; i < kPfB; ++i) {
-    const int b = min(tid + i * nthr, bblocks - 1);
-    const int nb = b & ((1 << lgnbn) - 1), kb = b >> lgnbn;
-    boff[i] = static_cast<int64_t>(kb << LGV) * a.N + (nb << LGV);
-    bq0[i] = ((nb << LGV) << LGCPR) + kb;
-  }
-
-  u32x4 ra[kPfA];
-  u32x4 rb[kPfB * VEC];
-
-  auto gload = [&](int l) __attribute__((always_inline)) {
-    const int64_t kbase = (static_cast<int64_t>(l) * a.kSplit + z) * a.BK;
-    const T* bg = Bg + kbase * a.N;
-    const T* ag = Ag + kbase + aoff0;
-#pragma unroll
-    for (int i = 0; i < kPfA; ++i)
-      if (i < na) ra[i] = *reinterpret_cast<const u32x4*>(ag + i * astride);
-#pragma unroll
-    for (int i = 0; i < kPfB; ++i)
-      if (i < nbb) {
-#pragma unroll
-        for (int j = 0; j < VEC; ++j)
-          rb[i * VEC + j] = *reinterpret_cast<const u32x4*>(bg + boff[i] + j * a.N);
-      }
-  };
-
-  auto lstore = [&](int buf) __attribute__((always_inline)) {
-    u32x4* as = lds + buf * stage;
-    u32x4* bs = as + achunks;
-#pragma unroll
-    for (int i = 0; i < kPfA; ++i)
-      if (i < na) as[swz(ta + i * nthr)] = ra[i];
-#pragma unroll
-    for (int i = 0; i < kPfB; ++i)
-      if (i < nbb) {
-        u32x4 t[VEC];
-        transpose_block(&rb[i * VEC], t);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) bs[swz(bq0[i] + (j << LGCPR))] = t[j];
-      }
-  };
-
-  // Tiles larger than the staging registers: load and store in rounds.
-  auto load_rounds = [&](int l, int buf) __attribute__((always_inline)) {
-    const int64_t kbase = (static_cast<int64_t>(l) * a.kSplit + z) * a.BK;
-    u32x4* as = lds + buf * stage;
-    u32x4* bs = as + achunks;
-    for (int e = tid; e < achunks; e += nthr)
-      as[swz(e)] = *reinterpret_cast<const u32x4*>(
-          Ag + static_cast<int64_t>(e >> LGCPR) * a.K + kbase + ((e & (CPR - 1)) << LGV));
-    for (int b = tid; b < bblocks; b += nthr) {
-      const int nb = b & ((1 << lgnbn) - 1), kb = b >> lgnbn;
-      const T* src = Bg + (kbase + (kb << LGV)) * a.N + (nb << LGV);
-      u32x4 r[VEC], t[VEC];
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) r[j] = *reinterpret_cast<const u32x4*>(src + j * a.N);
-      transpose_block(r, t);
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) bs[swz((((nb << LGV) + j) << LGCPR) + kb)] = t[j];
-    }
-  };
-
-  acc_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
-
-  // Fragment addressing. Row r, chunk ch = cs·G + grp sits at slot
-  // swz(r·CPR + ch) = ((X_j ^ (cs·G & 7)) + (cs·G & ~7)) with
-  // X_j = swz(r·CPR + grp + 8j) − 8j for line j = (cs·G) / 8 of the row.
-  const int grp = lane / I;
-  int xa[TM][NLINE], xb[TN][NLINE];
-#pragma unroll
-  for (int t = 0; t < TM; ++t)
-#pragma unroll
-    for (int j = 0; j < NLINE; ++j) {
-      const int q0 = ((wm * a.WM + t * I + (lane % I)) << LGCPR) + grp + 8 * j;
-      xa[t][j] = swz(q0) - 8 * j;
-    }
-#pragma unroll
-  for (int t = 0; t < TN; ++t)
-#pragma unroll
-    for (int j = 0; j < NLINE; ++j) {
-      const int q0 = ((wn * a.WN + t * I + (lane % I)) << LGCPR) + grp + 8 * j;
-      xb[t][j] = swz(q0) - 8 * j;
-    }
-
-  u32x4 fa[2][TM], fb[2][TN];
-  auto load_frags = [&](const u32x4* as, int cs, int slot) __attribute__((always_inline)) {
-    const u32x4* bs = as + achunks;
-    const int c = cs * G;
-    const int j = CPR >= 8 ? (c >> 3) : 0;
-#pragma unroll
-    for (int t = 0; t < TM; ++t) fa[slot][t] = as[(xa[t][j] ^ (c & 7)) + (c & ~7)];
-#pragma unroll
-    for (int t = 0; t < TN; ++t) fb[slot][t] = bs[(xb[t][j] ^ (c & 7)) + (c & ~7)];
-  };
-  auto mfmas = [&](int slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = mfma_bf16(__builtin_bit_cast(bf16x8, fa[slot][i]),
-                              __builtin_bit_cast(bf16x8, fb[slot][j]), acc[i][j]);
-  };
-
-  auto compute = [&](const u32x4* as) __attribute__((always_inline)) {
-#pragma unroll
-    for (int cs = 0; cs < NCS; ++cs) {
-      if (cs + 1 < NCS) load_frags(as, cs + 1, (cs + 1) & 1);
-      mfmas(cs & 1);
-    }
-  };
-
-  // Main loop: every stage but the last is one straight-line block — the
-  // next stage's global loads, this stage's LDS fragments and MFMAs, the
-  // next stage's LDS stores — so the scheduler can interleave them.
-  auto main_loop = [&](auto dbuf_tag) __attribute__((always_inline)) {
-    constexpr bool DB = decltype(dbuf_tag)::value;
-    gload(0);
-    lstore(0);
-    __syncthreads();
-    load_frags(lds, 0, 0);
-    int l = 0;
-    for (; l + 1 < a.kLoop; ++l) {
-      const int cur = DB ? (l & 1) : 0;
-      const int nxt = DB ? (cur ^ 1) : 0;
-      gload(l + 1);
-      // keep the next stage's loads ahead of this stage's MFMAs
-      __builtin_amdgcn_sched_barrier(0);
-      compute(lds + cur * stage);
-      if constexpr (!DB) __syncthreads();
-      lstore(nxt);
-      __syncthreads();
-      load_frags(lds + nxt * stage, 0, 0);
-    }
-    compute(lds + (DB ? (l & 1) : 0) * stage);
-  };
-
-  if (prefetch) {
-    if (a.dbuf)
-      main_loop(std::true_type{});
-    else
-      main_loop(std::false_type{});
-  } else {
-    load_rounds(0, 0);
-    __syncthreads();
-    load_frags(lds, 0, 0);
-    for (int l = 0; l < a.kLoop; ++l) {
-      const int cur = a.dbuf ? (l & 1) : 0;
-      compute(lds + cur * stage);
-      if (l + 1 < a.kLoop) {
-        if (!a.dbuf) __syncthreads();
-        const int nxt = a.dbuf ? (cur ^ 1) : 0;
-        load_rounds(l + 1, nxt);
-        __syncthreads();
-        load_frags(lds + nxt * stage, 0, 0);
-      }
-    }
-  }
-
-  float* Cw = a.C + static_cast<int64_t>(gm) * a.BM * a.N + static_cast<int64_t>(gn) * a.BN;
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int e = 0; e < NACC; ++e) {
-        const int r = wm * a.WM + i * I + out_row<I>(lane, e);
-        const int c = wn * a.WN + j * I + (lane % I);
-        put(a.atomic != 0, Cw + static_cast<int64_t>(r) * a.N + c, acc[i][j][e]);
-      }
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1060,31 +806,40 @@ __device__ __forceinline__ void gemm_fast_dl(const KArgs& a, char* smem) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 fast path: direct global→LDS loads into a ring
+// Fast path with direct global→LDS loads, any stage (fp32, bf16)
 // ---------------------------------------------------------------------------
 //
 // Tiles reach LDS by global_load_lds_dwordx4 (64 consecutive 16-byte slots a
 // wavefront instruction), never through registers, into a ring of ns stages
-// that keeps ns − 1 stages of loads in flight; one barrier a stage.
-// A row-major: [m][k] chunks of 4 k, row r's chunks XOR-ed by fswz(r), read 16
-// bytes a lane: the 4 k of a chunk feed 4 MFMAs, lane group g holding chunk
-// cs·G + g. B (and a K-major A) keep their [k][n] rows, split into one panel
-// per wavefront column of WN = TN·I columns so that every row stride is a
-// compile-time constant; a lane reads its column of the same 4 k with 4-byte
-// reads (consecutive lanes, consecutive banks). fp32 MFMAs take 32 (16×16×4)
-// or 64 cycles (32×32×2), so the extra LDS instructions that the untransposed
-// B costs stay below the matrix pipe's time: with one wavefront a SIMD and one
-// MFMA tile each, 16 of 128 (16×16) or 256 (32×32) cycles per chunk-step.
+// that keeps ns − 1 stages of loads in flight; one barrier a stage. The loads
+// of a stage need not divide evenly over the wavefronts.
+// A row-major: [m][k] chunks of 16 bytes, row r's chunks XOR-ed by fswz(r) (bf16
+// with 16×16 MFMA and two or more chunk-steps: the planes of gemm_fast_dl), read
+// 16 bytes a lane. B (and a K-major A) keep their [k][n] rows, split into one
+// panel per wavefront column of WN = TN·I columns so that every row stride is a
+// compile-time constant. bf16 panels are read with the transposing LDS read
+// (chunks of row k XOR-ed by bswz(k)). fp32: the 4 k of a chunk of A feed 4
+// MFMAs, lane group g holding chunk cs·G + g, and a lane reads its column of
+// the same 4 k with 4-byte reads (consecutive lanes, consecutive banks); fp32
+// MFMAs take 32 (16×16×4) or 64 cycles (32×32×2), so the extra LDS
+// instructions stay below the matrix pipe's time: with one wavefront a SIMD and
+// one MFMA tile each, 16 of 128 (16×16) or 256 (32×32) cycles per chunk-step.
 // With 16×16 MFMA the two lane groups of a half-wavefront read rows 4 apart,
 // a multiple of 256 bytes: odd groups' 16 columns are stored in the other half
-// of a 128-byte line (panels of 32 columns or more).
+// of a 128-byte line.
 //
-// Bound by the fp32 matrix pipe (157 TFLOP/s) where the tiles fill the chip,
-// by the launch and one trip to memory (about 5 µs) where K is short. Against
-// the register-staged form it replaced (loads one stage ahead, transposed in
-// registers, spilled from 64 accumulators on): 2048³ 158 -> 128 µs
-// (134 TFLOP/s), 1024³ 30.6 -> 23.0 µs, K-major 28.6 -> 21.5 µs,
-// 128×2048×2048 in 32×32×32 tiles 44.7 -> 24.6 µs.
+// Bound by the matrix pipe where the tiles fill the chip (fp32), by the operand
+// stream into LDS (bf16), by the launch and one trip to memory (about 5 µs)
+// where K is short. Against the register-staged form it replaced (loads one
+// stage ahead, transposed in registers, spilled from 64 accumulators on): fp32
+// 2048³ 158 -> 126 µs (137 TFLOP/s), 1024³ 31.3 -> 20.4 µs, K-major 31.7 ->
+// 20.8 µs; bf16 3136×4096×1024 in 64×256×32 tiles, 8 wavefronts, 186 -> 55 µs,
+// 1024×512×4096 in 64×32×64 tiles 78 -> 28 µs. Against gemm_fast_dl's loop
+// with a branch per load: 512×4096×4096 in 128×64×64 tiles (6 loads a
+// wavefront and stage) 34.8 -> 31 µs; at 2 and 3 loads that loop is up to 12 %
+// faster (128×2624×3456 in 32×32×32 tiles 32.3 against 36.6 µs), and at the
+// counts it is specialised for 8 % (4096³ in 256×256×32 tiles 115 against
+// 131 µs), so those stay there.
 
 // XOR of a row-major A row's chunk index: 8 consecutive rows read at the same
 // chunk hit the 8 distinct 16-byte slots of 128 bytes.
@@ -1118,14 +873,17 @@ constexpr bool ring_needs(int nh) {
   return false;
 }
 
-template <int I, int TM, int TN, int CPR, bool AK>
-__device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
+template <int DT, int I, int TM, int TN, int CPR, bool AK>
+__device__ __forceinline__ void gemm_ring(const KArgs& a, char* smem) {
+  static_assert(DT == 0 || !AK, "the K-major-A ring is fp32 only");
   using acc_t = typename AccT<I>::type;
+  constexpr int VEC = Elem<DT>::VEC, SZ = 16 / VEC;
   constexpr int G = 64 / I;
   constexpr int NCS = CPR / G;  // chunk-steps per stage
   constexpr int LGCPR = ilog2c<CPR>();
-  constexpr int BK = CPR * 4;
+  constexpr int BK = CPR * VEC;
   constexpr int WM = TM * I, WN = TN * I;
+  constexpr bool PLANES = DT == 1 && I == 16 && NCS >= 2;
   static_assert(NCS >= 1, "stage shallower than one MFMA K step");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1136,7 +894,7 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
   int gm, gn;
   tile_of(a, gm, gn);
   const int z = blockIdx.y;
-  const int BM = a.BM, BN = a.BN, ns = a.ns;
+  const int BM = a.BM, BN = a.BN, ns = a.ns, kLoop = a.kLoop;
   const uint32_t bbase = static_cast<uint32_t>(BM << LGCPR) * 16u;  // B inside a slot, bytes
   const uint32_t stage16 = bbase + (static_cast<uint32_t>(BN << LGCPR) * 16u);
   const uint32_t lds0 = static_cast<uint32_t>(
@@ -1144,96 +902,86 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
 
   // Origins of this workgroup's tiles in bytes, and the strides of consecutive
   // stages of this split-K slice.
-  const uint64_t lda = static_cast<uint64_t>(AK ? a.M : a.K) * 4u;
-  const uint64_t ldb = static_cast<uint64_t>(a.N) * 4u;
-  const uint64_t stepA = static_cast<uint64_t>(a.kSplit) * BK * (AK ? lda : 4u);
+  const uint64_t lda = static_cast<uint64_t>(AK ? a.M : a.K) * SZ;
+  const uint64_t ldb = static_cast<uint64_t>(a.N) * SZ;
+  const uint64_t stepA = static_cast<uint64_t>(a.kSplit) * BK * (AK ? lda : SZ);
   const uint64_t stepB = static_cast<uint64_t>(a.kSplit) * BK * ldb;
-  const uint64_t orgA = uniform_ptr(a.A) + static_cast<uint64_t>(gm) * BM * (AK ? 4u : lda) +
-                        static_cast<uint64_t>(z) * BK * (AK ? lda : 4u);
-  const uint64_t orgB = uniform_ptr(a.B) + static_cast<uint64_t>(gn) * BN * 4u +
+  const uint64_t orgA = uniform_ptr(a.A) + static_cast<uint64_t>(gm) * BM * (AK ? SZ : lda) +
+                        static_cast<uint64_t>(z) * BK * (AK ? lda : SZ);
+  const uint64_t orgB = uniform_ptr(a.B) + static_cast<uint64_t>(gn) * BN * SZ +
                         static_cast<uint64_t>(z) * BK * ldb;
 
-  // This wavefront's share of one operand's loads of a stage: instructions
-  // b0, b0 + db, … of a block of rows of C chunks (a row-major A's tile, rows
-  // of CPR chunks of k; a panel, rows of W / 4 chunks of columns). Instruction
-  // b covers chunks 64·b … 64·b + 63 of the block.
+  // A wavefront's loads of one operand of a stage: instructions b0, b0 + db, …
+  // of a block of LDS slots, 64 of them each. The block is a row-major A's
+  // whole tile or one panel; consecutive wavefronts take the same instruction
+  // of consecutive panels (never more than there are wavefronts), then the
+  // next. B's start with the last wavefront, so that a short A and a short B
+  // are not both on the first ones.
   struct Share {
-    int cnt, b0, db;
-    uint32_t row, pos;  // per lane: its row's and chunk's bytes past the instruction's first
-    uint64_t base;      // the block's bytes from the stage's origin
-    uint32_t dst;       // … and from the slot's start
+    int cnt, b0, db, block;
   };
-  // Row-major A.
-  auto share_rows = [&](int w) __attribute__((always_inline)) {
-    Share h;
-    h.cnt = (((BM << LGCPR) >> 6) - w + nw - 1) / nw;
-    h.b0 = w;
-    h.db = nw;
-    h.row = static_cast<uint32_t>(lane >> LGCPR) * static_cast<uint32_t>(lda);
-    h.pos = static_cast<uint32_t>((lane & (CPR - 1)) ^ fswz<CPR>(lane >> LGCPR)) * 16u;
-    h.base = 0;
-    h.dst = 0;
-    return h;
+  auto share = [&](int w, int blocks, int insts) __attribute__((always_inline)) {
+    const int b0 = w / blocks, db = nw / blocks;
+    return Share{(insts - b0 + db - 1) / db, b0, db, w % blocks};
   };
-  // A [k][n] operand in `panels` (at most nw) panels of W columns, one after
-  // the other in LDS: consecutive wavefronts take the same rows of consecutive
-  // panels, then the next rows.
-  auto share_panels = [&](int w, int panels, uint64_t ld, auto wtag) __attribute__((always_inline)) {
-    constexpr int CW = decltype(wtag)::value / 4;  // chunks per row of a panel
-    constexpr int NPP = BK * CW / 64;              // instructions per panel
-    Share h;
-    const int panel = w % panels;
-    h.b0 = w / panels;
-    h.db = nw / panels;
-    h.cnt = (NPP - h.b0 + h.db - 1) / h.db;
-    const int pos = CW >= 64 ? lane : lane % CW, row = CW >= 64 ? 0 : lane / CW;
-    h.row = static_cast<uint32_t>(row) * static_cast<uint32_t>(ld);
-    h.pos = static_cast<uint32_t>(flip_panel<I, CW>() ? pos ^ (row & 4) : pos) * 16u;
-    h.base = static_cast<uint64_t>(panel * CW) * 16u;
-    h.dst = static_cast<uint32_t>(panel * NPP) * 1024u;
-    return h;
-  };
-  constexpr std::integral_constant<int, WM> wm_tag{};
-  constexpr std::integral_constant<int, WN> wn_tag{};
-  Share ha;
-  if constexpr (AK)
-    ha = share_panels(wave, a.wavesM, lda, wm_tag);
-  else
-    ha = share_rows(wave);
-  // (the last wavefronts first, so that a short A and a short B are not both
-  // on the first ones)
-  Share hb = share_panels(nw - 1 - wave, a.wavesN, ldb, wn_tag);
-  hb.dst += bbase;
+  constexpr int NPA = CPR * WM / 64, NPB = CPR * WN / 64;  // instructions per panel
+  const Share ha = AK ? share(wave, a.wavesM, NPA) : share(wave, 1, (BM << LGCPR) >> 6);
+  const Share hb = share(nw - 1 - wave, a.wavesN, NPB);
   const int cnt = ha.cnt + hb.cnt;
-  // Load j of a share: its uniform bytes from the stage's origin, and the
-  // bytes (0 or 64) that its rows' part of the XOR changes a lane's chunk by:
-  // bit 2 of its first row, where an instruction has fewer than 8 rows.
-  constexpr int CA = AK ? WM / 4 : CPR, CB = WN / 4;
-  constexpr bool kFlipA = AK ? flip_panel<I, CA>() && CA == 16 : CPR == 16;
-  constexpr bool kFlipB = flip_panel<I, CB>() && CB == 16;
-  auto at_a = [&](int j) __attribute__((always_inline)) {
-    const uint32_t s = static_cast<uint32_t>(ha.b0 + j * ha.db) << 6;
-    return ha.base + static_cast<uint64_t>(s / CA) * lda + (s % CA) * 16u;
+  // Where load j reads, from the stage's origin: a uniform part and a lane's
+  // (an instruction spans at most 32 rows), and where it writes in the slot.
+  struct Place {
+    uint64_t at;
+    uint32_t lane, dst;
   };
-  auto at_b = [&](int j) __attribute__((always_inline)) {
-    const uint32_t s = static_cast<uint32_t>(hb.b0 + j * hb.db) << 6;
-    return hb.base + static_cast<uint64_t>(s / CB) * ldb + (s % CB) * 16u;
+  auto panel_place = [&](const Share& h, int j, uint64_t ld, auto wtag, int insts) __attribute__((always_inline)) {
+    constexpr int C = decltype(wtag)::value / VEC;  // chunks per row of the panel
+    const int s = (h.b0 + j * h.db) << 6;
+    const int r0 = s / C, row = C >= 64 ? 0 : lane / C;
+    const int pos = C >= 64 ? s % C + lane : lane % C;
+    const int k = r0 + row;
+    const int x = DT == 1 ? bswz(k, C) : (flip_panel<I, C>() ? k & 4 : 0);
+    return Place{static_cast<uint64_t>(r0) * ld + static_cast<uint64_t>(h.block * C) * 16u,
+                 static_cast<uint32_t>(row) * static_cast<uint32_t>(ld) + static_cast<uint32_t>(pos ^ x) * 16u,
+                 static_cast<uint32_t>(h.block * insts + h.b0 + j * h.db) * 1024u};
   };
-  auto lane_a = [&](int j) __attribute__((always_inline)) {
-    const uint32_t r = (static_cast<uint32_t>(ha.b0 + j * ha.db) << 6) / CA;
-    return ha.row + (kFlipA ? ha.pos ^ ((r & 4) << 4) : ha.pos);
+  auto place_a = [&](int j) __attribute__((always_inline)) {
+    if constexpr (AK) {
+      return panel_place(ha, j, lda, std::integral_constant<int, WM>{}, NPA);
+    } else {
+      const int b = ha.b0 + j * ha.db, s = b << 6;
+      Place p;
+      p.dst = static_cast<uint32_t>(b) * 1024u;
+      if constexpr (PLANES) {
+        const int lgp = a.lgBM + 2, in = s & ((1 << lgp) - 1);  // slots per plane: 4·BM
+        const int q = swz(in + lane);
+        p.at = static_cast<uint64_t>(in >> 2) * lda + static_cast<uint64_t>(s >> lgp) * 64u;
+        p.lane = static_cast<uint32_t>((q >> 2) - (in >> 2)) * static_cast<uint32_t>(lda) +
+                 static_cast<uint32_t>(q & 3) * 16u;
+      } else {
+        const int r0 = s >> LGCPR, row = lane >> LGCPR;
+        p.at = static_cast<uint64_t>(r0) * lda;
+        p.lane = static_cast<uint32_t>(row) * static_cast<uint32_t>(lda) +
+                 static_cast<uint32_t>((lane & (CPR - 1)) ^ fswz<CPR>(r0 + row)) * 16u;
+      }
+      return p;
+    }
   };
-  auto lane_b = [&](int j) __attribute__((always_inline)) {
-    const uint32_t r = (static_cast<uint32_t>(hb.b0 + j * hb.db) << 6) / CB;
-    return hb.row + (kFlipB ? hb.pos ^ ((r & 4) << 4) : hb.pos);
+  auto place_b = [&](int j) __attribute__((always_inline)) {
+    Place p = panel_place(hb, j, ldb, std::integral_constant<int, WN>{}, NPB);
+    p.dst += bbase;
+    return p;
   };
-  auto dst_a = [&](int j) { return ha.dst + static_cast<uint32_t>(ha.b0 + j * ha.db) * 1024u; };
-  auto dst_b = [&](int j) { return hb.dst + static_cast<uint32_t>(hb.b0 + j * hb.db) * 1024u; };
-
   // All of this wavefront's loads of a stage, back to back, at any distance.
   auto issue_all = [&](uint64_t ga, uint64_t gb, uint32_t slot) __attribute__((always_inline)) {
-    for (int j = 0; j < ha.cnt; ++j) dma_load16_if(1, 0, lane_a(j), ga + at_a(j), slot + dst_a(j));
-    for (int j = 0; j < hb.cnt; ++j) dma_load16_if(1, 0, lane_b(j), gb + at_b(j), slot + dst_b(j));
+    for (int j = 0; j < ha.cnt; ++j) {
+      const Place p = place_a(j);
+      dma_load16_if(1, 0, p.lane, ga + p.at, slot + p.dst);
+    }
+    for (int j = 0; j < hb.cnt; ++j) {
+      const Place p = place_b(j);
+      dma_load16_if(1, 0, p.lane, gb + p.at, slot + p.dst);
+    }
   };
 
   acc_t acc[TM][TN];
@@ -1242,53 +990,91 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
 
-  // This lane's read offsets inside a slot. [k][n] panels: rows
-  // (cs·G + grp)·4 + q, column t·I + lane % I of the wavefront's panel.
+  // This lane's read offsets inside a slot. fp32 [k][n] panels: rows
+  // (cs·G + grp)·4 + q, column t·I + lane % I of the wavefront's panel; bf16:
+  // the transposing read's (input lane i of a 16-lane group covers row
+  // k0 + (i >> 2), 4 rows further for the second read, columns 4(i & 3) on).
   const int grp = lane / I, l0 = lane % I;
   auto panel_read = [&](int wi, int t, auto w) __attribute__((always_inline)) {
-    constexpr int W = decltype(w)::value;
-    int col = t * I + l0;
-    if constexpr (flip_panel<I, W / 4>()) col ^= (grp & 1) << 4;
-    return static_cast<uint32_t>(wi * (BK * W) + grp * 4 * W + col) * 4u;
+    constexpr int W = decltype(w)::value, C = W / VEC;
+    const int block = wi * (BK * W) * SZ;
+    if constexpr (DT == 1) {
+      const int i16 = lane & 15, g16 = lane >> 4;
+      const int k = (I == 32 ? (g16 >> 1) : g16) * 8 + (i16 >> 2);
+      const int col = t * I + (I == 32 ? 16 * (g16 & 1) : 0) + 4 * (i16 & 3);
+      return static_cast<uint32_t>(block + (k * C + ((col >> 3) ^ bswz(k, C))) * 16 + (col & 4) * 2);
+    } else {
+      int col = t * I + l0;
+      if constexpr (flip_panel<I, C>()) col ^= (grp & 1) << 4;
+      return static_cast<uint32_t>(block + (grp * 4 * W + col) * 4);
+    }
   };
   uint32_t xa[TM], xb[TN];
   const int af = fswz<CPR>(l0) ^ grp;  // I and the tile's rows are multiples of 16
+  const int plane = BM << 6;           // bytes of one chunk-step's plane
 #pragma unroll
   for (int t = 0; t < TM; ++t) {
+    const int row = wm * WM + t * I + l0;
     if constexpr (AK)
       xa[t] = panel_read(wm, t, std::integral_constant<int, WM>{});
+    else if constexpr (PLANES)
+      xa[t] = static_cast<uint32_t>(swz((row << 2) + grp)) * 16u;
     else
-      xa[t] = static_cast<uint32_t>(wm * WM + t * I + l0) * (CPR * 16u);
+      xa[t] = static_cast<uint32_t>(row) * (CPR * 16u);
   }
 #pragma unroll
   for (int t = 0; t < TN; ++t) xb[t] = bbase + panel_read(wn, t, std::integral_constant<int, WN>{});
 
-  f32x4 fa[2][TM], fb[2][TN];
+  u32x4 fa[2][TM], fb[2][TN];
   auto load_frags = [&](const char* st, int cs, int fs) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < TM; ++t) {
       if constexpr (AK) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          fa[fs][t][q] = *reinterpret_cast<const float*>(st + xa[t] + (cs * G * 4 + q) * WM * 4);
+          fa[fs][t][q] = *reinterpret_cast<const unsigned*>(st + xa[t] + (cs * G * 4 + q) * WM * 4);
+      } else if constexpr (PLANES) {
+        fa[fs][t] = *reinterpret_cast<const u32x4*>(st + cs * plane + xa[t]);
       } else {
-        fa[fs][t] = *reinterpret_cast<const f32x4*>(st + xa[t] + ((af ^ (cs * G)) << 4));
+        fa[fs][t] = *reinterpret_cast<const u32x4*>(st + xa[t] + ((af ^ (cs * G)) << 4));
       }
     }
 #pragma unroll
-    for (int t = 0; t < TN; ++t)
+    for (int t = 0; t < TN; ++t) {
+      if constexpr (DT == 1) {
+        s16x4 h[2];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        fb[fs][t][q] = *reinterpret_cast<const float*>(st + xb[t] + (cs * G * 4 + q) * WN * 4);
+        for (int hh = 0; hh < 2; ++hh)
+          h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (__attribute__((address_space(3))) s16x4*)(st + xb[t] + (cs * G * 8 + 4 * hh) * WN * 2));
+        fb[fs][t] = __builtin_bit_cast(u32x4, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          fb[fs][t][q] = *reinterpret_cast<const unsigned*>(st + xb[t] + (cs * G * 4 + q) * WN * 4);
+      }
+    }
   };
-  auto mfmas = [&](int fs, int q) __attribute__((always_inline)) {
+  // A chunk-step's MFMAs in SG groups: fp32, one per element of the chunks;
+  // bf16, runs of the TM·TN tiles.
+  constexpr int SG = DT == 0 || TM * TN >= 4 ? 4 : TM * TN;
+  auto mfmas = [&](int fs, int g) __attribute__((always_inline)) {
+    if constexpr (DT == 1) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+      for (int q = 0; q < TM * TN; ++q)
+        if (q * SG / (TM * TN) == g)
+          acc[q / TN][q % TN] = mfma_bf16(__builtin_bit_cast(bf16x8, fa[fs][q / TN]),
+                                          __builtin_bit_cast(bf16x8, fb[fs][q % TN]), acc[q / TN][q % TN]);
+    } else {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = mfma_f32(fa[fs][i][q], fb[fs][j][q], acc[i][j]);
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = mfma_f32(__builtin_bit_cast(f32x4, fa[fs][i])[g], __builtin_bit_cast(f32x4, fb[fs][j])[g],
+                               acc[i][j]);
+    }
   };
 
-  const int kLoop = a.kLoop;
   if (ns == 1) {
     // a stage that leaves no room for a second one, or the only one
     uint64_t ga = orgA, gb = orgB;
@@ -1302,7 +1088,7 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
         if (cs + 1 < NCS) load_frags(smem, cs + 1, (cs + 1) & 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) mfmas(cs & 1, q);
+        for (int g = 0; g < SG; ++g) mfmas(cs & 1, g);
         __builtin_amdgcn_sched_barrier(0);
       }
       waitcnt_lgkm0();
@@ -1314,17 +1100,14 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
     // MFMAs; the loads of stage l + ns, into the slot that every wavefront has
     // read by then, are issued from that chunk-step on, over a window of NCS
     // chunk-steps that ends before the next boundary.
-    const int npro = min(ns - 1, kLoop);
-    for (int l = 0; l < npro; ++l)
-      issue_all(orgA + l * stepA, orgB + l * stepB, lds0 + l * stage16);
     const uint32_t ring = ns * stage16;
 
     // NH: the loads of A, and of B, that a wavefront issues per stage, evenly
-    // spread over a window's 4·NCS MFMA groups as straight-line code; a
+    // spread over a window's NCS·SG MFMA groups as straight-line code; a
     // wavefront with fewer (and every one after the last stage) issues the
     // rest with no lane enabled, so the count is the same everywhere. With one
-    // wavefront a SIMD a branch in every group cost a fifth of the loop
-    // (1024³, 64×64×64 tiles: 20.8 µs per 1024 of K with branches, 16.9 µs
+    // wavefront a SIMD a branch in every group cost a fifth of the loop (fp32
+    // 1024³, 64×64×64 tiles: 20.8 µs per 1024 of K with branches, 16.9 µs
     // without, 14 µs of MFMA). NH = 0: more loads than the offsets kept for
     // them, or offsets past 32 bits: all at once after the boundary.
     auto run = [&](auto nh) __attribute__((always_inline)) {
@@ -1332,51 +1115,57 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
       uint32_t oa[NH ? NH : 1], ob[NH ? NH : 1];
 #pragma unroll
       for (int i = 0; i < NH; ++i) {
-        oa[i] = lane_a(i) + static_cast<uint32_t>(at_a(i));
-        ob[i] = lane_b(i) + static_cast<uint32_t>(at_b(i));
+        const Place p = place_a(i), q = place_b(i);
+        oa[i] = p.lane + static_cast<uint32_t>(p.at);
+        ob[i] = q.lane + static_cast<uint32_t>(q.at);
       }
       struct Window {
         uint64_t ga, gb;
         uint32_t da, db;  // the next load's place in the slot
         int na, nb;       // loads with their lanes enabled
       };
+      const uint32_t fa0 = place_a(0).dst, fb0 = place_b(0).dst;
       const uint32_t sda = static_cast<uint32_t>(ha.db) * 1024u, sdb = static_cast<uint32_t>(hb.db) * 1024u;
       auto window = [&](uint64_t ga, uint64_t gb, uint32_t slot, bool on) __attribute__((always_inline)) {
         if (NH == 0 && on) issue_all(ga, gb, slot);
-        return Window{ga, gb, slot + dst_a(0), slot + dst_b(0), on ? ha.cnt : 0, on ? hb.cnt : 0};
+        return Window{ga, gb, slot + fa0, slot + fb0, on ? ha.cnt : 0, on ? hb.cnt : 0};
       };
-      // the loads that follow MFMA group u of a window
+      // the loads that follow MFMA group u of a window (u < 0: all of them)
       auto group = [&](Window& w, int u) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NH; ++i) {
-          if (2 * i * 4 * NCS / (2 * NH) == u) {
+          if (u < 0 || i * NCS * SG / NH == u) {
             dma_load16_if(w.na, i, oa[i], w.ga, w.da);
             w.da += sda;
           }
-          if ((2 * i + 1) * 4 * NCS / (2 * NH) == u) {
+          if (u < 0 || (2 * i + 1) * NCS * SG / (2 * NH) == u) {
             dma_load16_if(w.nb, i, ob[i], w.gb, w.db);
             w.db += sdb;
           }
         }
       };
-      // stage l + 2 may still be on its way (ns = 3)
+      // at most `after` stages past the one wanted may still be on their way
+      const int keep = __builtin_amdgcn_readfirstlane((ns - 2) * 2 * NH);
       auto wait_stage = [&](int l) __attribute__((always_inline)) {
-        if (ns == 2)
-          waitcnt_vm<0>();
-        else if constexpr (NH > 0)
+        if constexpr (NH == 0)
+          wait_vm_at_most(__builtin_amdgcn_readfirstlane(max(min(ns - 2, kLoop - 2 - l), 0) * cnt));
+        else if (ns == 3)
           waitcnt_vm<2 * NH>();
         else
-          wait_vm_at_most(__builtin_amdgcn_readfirstlane(l + 2 < kLoop ? cnt : 0));
+          wait_vm_at_most(keep);
       };
-      // stage 0 has landed when at most the other npro − 1 are outstanding
-      wait_vm_at_most(__builtin_amdgcn_readfirstlane((npro - 1) * cnt));
+      Window w{};
+      for (int l = 0; l + 1 < ns; ++l) {
+        w = window(orgA + l * stepA, orgB + l * stepB, lds0 + l * stage16, l < kLoop);
+        group(w, -1);
+      }
+      wait_stage(-1);
       ring_barrier();
-      Window w = window(orgA + static_cast<uint64_t>(ns - 1) * stepA,
-                        orgB + static_cast<uint64_t>(ns - 1) * stepB, lds0 + (ns - 1) * stage16,
-                        ns - 1 < kLoop);
+      w = window(orgA + static_cast<uint64_t>(ns - 1) * stepA, orgB + static_cast<uint64_t>(ns - 1) * stepB,
+                 lds0 + (ns - 1) * stage16, ns - 1 < kLoop);
       load_frags(smem, 0, 0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) group(w, q);
+      for (int g = 0; g < SG; ++g) group(w, g);
       uint32_t cur_b = 0;  // this stage's slot, bytes from the ring's start
       for (int l = 0; l < kLoop; ++l) {
         const char* st = smem + cur_b;
@@ -1386,9 +1175,9 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
           load_frags(st, cs + 1, (cs + 1) & 1);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            mfmas(cs & 1, q);
-            group(w, 4 + 4 * cs + q);
+          for (int g = 0; g < SG; ++g) {
+            mfmas(cs & 1, g);
+            group(w, SG + SG * cs + g);
           }
         }
         const bool more = l + 1 < kLoop;
@@ -1402,9 +1191,9 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
         }
         w = window(w.ga + stepA, w.gb + stepB, lds0 + cur_b, l + ns < kLoop);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          mfmas((NCS - 1) & 1, q);
-          group(w, q);
+        for (int g = 0; g < SG; ++g) {
+          mfmas((NCS - 1) & 1, g);
+          group(w, g);
         }
         if constexpr (NCS == 1) {
           if (more) load_frags(smem + nx_b, 0, 0);
@@ -1413,8 +1202,7 @@ __device__ __forceinline__ void gemm_ring_f32(const KArgs& a, char* smem) {
       }
     };
     // The most loads of one operand that any wavefront of the workgroup has.
-    const int most = max(((BM << LGCPR) + 64 * nw - 1) / (64 * nw),
-                         ((BN << LGCPR) + 64 * nw - 1) / (64 * nw));
+    const int most = max(((BM << LGCPR) + 64 * nw - 1) / (64 * nw), ((BN << LGCPR) + 64 * nw - 1) / (64 * nw));
     auto run_if = [&](auto nh) __attribute__((always_inline)) {
       if constexpr (ring_needs<I, TM, TN, CPR>(decltype(nh)::value)) run(nh);
     };
@@ -1725,10 +1513,8 @@ __global__ void __launch_bounds__((launch_threads<I, TM, TN, CPR>())) gemm_kerne
   char* smem = reinterpret_cast<char*>(gt_smem);
   if constexpr (CPR == 0) {
     gemm_generic<DT, I, TM, TN>(a, smem);
-  } else if constexpr (DT == 0) {
-    gemm_ring_f32<I, TM, TN, CPR, false>(a, smem);
   } else {
-    gemm_fast<I, TM, TN, CPR>(a, smem);
+    gemm_ring<DT, I, TM, TN, CPR, false>(a, smem);
   }
 }
 
@@ -1744,7 +1530,7 @@ template <int DT, int I, int TM, int TN, int CPR>
 __global__ void __launch_bounds__((launch_threads<I, TM, TN, CPR>())) gemm_kernel_akm(KArgs a) {
   static_assert(DT == 0, "the K-major-A fast path is fp32 only");
   extern __shared__ u32x4 gt_smem[];
-  gemm_ring_f32<I, TM, TN, CPR, true>(a, reinterpret_cast<char*>(gt_smem));
+  gemm_ring<0, I, TM, TN, CPR, true>(a, reinterpret_cast<char*>(gt_smem));
 }
 
 // bf16 fast path with direct global→LDS loads: a kernel of its own, so that
@@ -1787,7 +1573,7 @@ hipError_t launch_gemm(const KArgs& a, dim3 grid, dim3 block, size_t lds, hipStr
     return launch_one(gemm_kernel_akm<DT, I, TM, TN, CPR>, attr_akm, a, grid, block, lds, s);
   } else {
     if constexpr (DT == 1 && CPR > 0) {
-      if (a.dl) {
+      if (a.dlk) {
         static std::atomic<uint64_t> attr_dl{0};
         return launch_one(gemm_kernel_dl<I, TM, TN, CPR>, attr_dl, a, grid, block, lds, s);
       }

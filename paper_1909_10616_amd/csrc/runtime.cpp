@@ -113,13 +113,16 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   const int64_t cpr = L.BK / vec;  // 16-byte chunks per LDS row
   const bool cpr_ok = L.BK % vec == 0 && (cpr == 2 || cpr == 4 || cpr == 8 || cpr == 16);
   // (a K-major A needs 16-byte m chunks, M % vec; its fast path is fp32 only;
-  // the fp32 ring's loads keep 32-bit offsets over the up to 32 rows of one
-  // instruction)
+  // the ring's loads keep 32-bit offsets over the rows of one instruction, 64
+  // chunks of a tile or panel)
+  const int64_t rows_a = std::max<int64_t>(
+      akm ? 64 * vec / std::max<int64_t>(L.repM * L.blkM, 1) : 64 / std::max<int64_t>(cpr, 1), 16);
+  const int64_t rows_b = std::max<int64_t>(64 * vec / std::max<int64_t>(L.repN * L.blkN, 1), 1);
   const bool fast = L.blkM % L.I == 0 && L.blkN % L.I == 0 && L.kBlk % L.IK == 0 &&
                     L.BK % (vec * G) == 0 && cpr_ok && L.BN % vec == 0 && K % vec == 0 &&
                     N % vec == 0 && L.W <= 8 && aligned16(A) && aligned16(B) &&
                     (!akm || (dt == GT_F32 && L.BM % vec == 0 && M % vec == 0)) &&
-                    (dt == GT_BF16 || std::max({akm ? M : K, N}) < (int64_t{1} << 25));
+                    std::max(rows_a * (akm ? M : K), rows_b * N) * L.elem < (int64_t{1} << 32);
   const int64_t stage_bytes = (L.BM * L.BK + L.BK * L.BN) * L.elem;
   const bool dbuf = L.kLoop >= 2 && 2 * stage_bytes <= kLdsMax;
   // bf16 fast path with direct global->LDS loads into a ring of ns stages:
@@ -132,8 +135,15 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   const bool dl = fast && dt == GT_BF16 && !akm && achunks % (64 * L.W) == 0 &&
                   bchunks % (64 * L.W) == 0 && dl_inst / L.W <= dl_inst_cap(L.acc) && ns_dl >= 2 &&
                   L.BM * K < (int64_t{1} << 31) && L.BK * N < (int64_t{1} << 31);
-  const bool ring = dl || (fast && dt == GT_F32);
-  const int64_t ns = dl ? ns_dl : (ring ? f32_ring_stages(L, stage_bytes) : 0);
+  // which kernel: the ring above is specialised for two counts of loads per
+  // wavefront and stage, and with 2 or 3 its loop of checked loads beats the
+  // general ring's masked ones (measured beside that kernel)
+  const int64_t per_wave = dl_inst / L.W, cap = dl_inst_cap(L.acc);
+  const bool dlk = dl && (per_wave == cap || per_wave == cap / 2 || per_wave <= 3);
+  const int64_t ns = dl ? ns_dl
+                        : !fast ? 0
+                        : dt == GT_F32 ? f32_ring_stages(L, stage_bytes)
+                                       : std::max<int64_t>(1, std::min(ns_dl, L.kLoop));
 
   KArgs& a = out->args;
   std::memset(&a, 0, sizeof(a));
@@ -173,9 +183,10 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   a.lgBM = ilog2(L.BM);
   a.bVec = (L.BN % vec == 0 && N % vec == 0 && aligned16(B)) ? vec : 1;
   a.dl = dl ? 1 : 0;
+  a.dlk = dlk ? 1 : 0;
   a.ns = static_cast<int32_t>(ns);
   // bytes from a stage's origins to its last row of A (row-major) or k row
-  a.wide = std::max({akm ? L.BK * M : L.BM * K, L.BK * N}) >= (int64_t{1} << 30) ? 1 : 0;
+  a.wide = std::max({akm ? L.BK * M : L.BM * K, L.BK * N}) * L.elem >= (int64_t{1} << 32) ? 1 : 0;
 
   a.stream = !fast && stream_serves(L, M, N, K, dt, akm, aligned16(A), aligned16(B),
                                     stage_bytes * (dbuf ? 2 : 1))
@@ -184,7 +195,7 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
 
   out->grid = dim3(static_cast<unsigned>(L.gridM * L.gridN), static_cast<unsigned>(L.kSplit), 1);
   out->block = dim3(static_cast<unsigned>(64 * L.W), 1, 1);
-  out->lds = static_cast<size_t>(stage_bytes * (ring ? ns : (dbuf ? 2 : 1)));
+  out->lds = static_cast<size_t>(stage_bytes * (fast ? ns : (dbuf ? 2 : 1)));
   out->fast = fast;
   out->fn = find_gemm_kernel(dt, L.I, fast ? static_cast<int>(cpr) : 0,
                              static_cast<int>(L.TM), static_cast<int>(L.TN), fast && akm);

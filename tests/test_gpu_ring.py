@@ -1,4 +1,4 @@
-"""The fp32 ring kernel at the edges of its schedule and layouts, small
+"""The ring kernel (fp32, bf16) at the edges of its schedule and layouts, small
 integers (every order of the sums exact) against the oracle, bit for bit."""
 import numpy as np
 import pytest
@@ -46,15 +46,36 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("kmajor", [False, True])
-@pytest.mark.parametrize("case", CASES, ids=[str(c[:3]).replace(" ", "") for c in CASES])
-def test_ring_bit_exact(gt, orc, case, kmajor):
+# bf16 stages the evenly shared kernel does not take: uneven shares, more loads
+# than it holds, 4 to 7 of them, one-stage and two-stage rings, the MFMA sizes
+BF16 = [
+    *[((2, 8, 1, 16), (2, 1, 1, 32), (k, 1, 1, 32), 16) for k in (1, 2, 5, 9, 17)],
+    *[((2, 8, 1, 16), (2, 1, 1, 32), (k, 1, 2, 32), 16) for k in (1, 3, 9)],
+    ((2, 8, 1, 16), (2, 1, 1, 16), (5, 1, 4, 32), 16),
+    ((2, 1, 1, 16), (2, 8, 1, 16), (5, 1, 1, 32), 16),
+    *[((2, 1, 1, 32), (2, 1, 1, 32), (k, 1, 8, 16), 32) for k in (1, 2, 3, 9)],
+    ((2, 1, 2, 16), (2, 1, 2, 16), (5, 1, 4, 32), 16),
+    ((2, 1, 1, 32), (2, 1, 8, 16), (5, 1, 2, 32), 16),
+    ((2, 1, 1, 32), (2, 1, 4, 32), (5, 1, 2, 16), 32),
+    ((2, 2, 2, 32), (2, 2, 1, 32), (9, 1, 2, 32), 32),       # 6 loads a wavefront
+    ((2, 2, 4, 32), (2, 4, 2, 32), (4, 1, 2, 32), 16),       # 8 of them spread over 8 wavefronts
+    ((1, 4, 2, 32), (1, 2, 4, 32), (3, 1, 4, 32), 16),       # one stage fills LDS
+    ((2, 1, 1, 32), (1, 1, 16, 32), (3, 1, 1, 16), 32),      # a panel of 512 columns
+    ((2, 1, 1, 16), (1, 1, 64, 16), (3, 1, 1, 32), 16),      # … of 1024
+    *[((2, 8, 1, 16), (2, 1, 1, 32), (k, 4, 1, 32), 16) for k in (1, 2, 5)],
+]
+ALL = [("f32", c, km) for c in CASES for km in (False, True)] + [("bf16", c, False) for c in BF16]
+
+
+@pytest.mark.parametrize("dtype,case,kmajor", ALL,
+                         ids=[f"{d}-{'k' if k else 'r'}-{i}" for i, (d, _, k) in enumerate(ALL)])
+def test_ring_bit_exact(gt, orc, dtype, case, kmajor):
     m, n, k, mf = case
     M, N, K = (int(np.prod(x)) for x in (m, n, k))
-    info = gt.lower((m, k, n, mf), M, N, K, gt.F32 | (gt.A_KMAJOR if kmajor else 0))
+    info = gt.lower((m, k, n, mf), M, N, K, gt.dtype_code(dtype) | (gt.A_KMAJOR if kmajor else 0))
     assert info["fast"] == 1 and info["ring"] >= 1, info
-    A, B = make_inputs(M, N, K, "f32", 23, "smallint")
-    ref = orc.gemm(raw_bytes(A), raw_bytes(B), M, N, K, "f32")
+    A, B = make_inputs(M, N, K, dtype, 23, "smallint")
+    ref = orc.gemm(raw_bytes(A), raw_bytes(B), M, N, K, dtype)
     Ad = (A.t().contiguous() if kmajor else A).cuda()
     C = torch.full((M, N), float("nan"), device="cuda")
     gt.gemm_run((m, k, n, mf), Ad, B.cuda(), C, a_kmajor=kmajor)
