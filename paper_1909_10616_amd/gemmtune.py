@@ -12,6 +12,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import struct
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "_lib", "libgemmtune.so")
@@ -165,7 +166,22 @@ def dtype_code(dtype) -> int:
     raise ValueError(f"unsupported dtype {dtype!r}")
 
 
+# gt_config's fields in order: the level counts and MFMA size, the three level
+# arrays, legit and reserved. One pack and one copy (0.9 µs) where filling the
+# structure field by field took 1.9 µs of every call.
+_CONFIG = struct.Struct(f"=4i{3 * MAXD}q2i")
+_PAD = tuple((0,) * (MAXD - d) for d in range(MAXD + 1))
+assert _CONFIG.size == ctypes.sizeof(gt_config)
+
+
 def to_c(cfg) -> gt_config:
+    try:
+        m, k, n, mfma = cfg
+        return gt_config.from_buffer_copy(_CONFIG.pack(
+            len(m), len(k), len(n), mfma, *m, *_PAD[len(m)], *k, *_PAD[len(k)], *n, *_PAD[len(n)],
+            0, 0))
+    except (struct.error, TypeError, ValueError, IndexError):
+        pass   # no MFMA size, values to convert, or too many levels
     c = gt_config()
     m, k, n = cfg[0], cfg[1], cfg[2]
     c.d_m, c.d_k, c.d_n = len(m), len(k), len(n)
@@ -262,6 +278,10 @@ def lower(cfg, M, N, K, dtype) -> dict:
 def _stream(stream):
     import torch
     if stream is None:
+        # the handle alone: a Stream object for it costs more than the rest of
+        # the call's argument handling
+        if torch.cuda.is_initialized():
+            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
@@ -273,15 +293,19 @@ def _operands(A, B, C, a_kmajor=False):
     for t, name in ((A, "A"), (B, "B"), (C, "C")):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous GPU tensor")
-    if A.dtype != B.dtype or A.dtype not in (torch.float32, torch.bfloat16):
+    dt = A.dtype
+    if dt is not B.dtype or (dt is not torch.float32 and dt is not torch.bfloat16):
         raise ValueError("A and B must both be float32 or both bfloat16")
-    if C.dtype != torch.float32:
+    if C.dtype is not torch.float32:
         raise ValueError("C must be float32")
-    K, M = A.shape if a_kmajor else A.shape[::-1]
+    if a_kmajor:
+        K, M = A.shape
+    else:
+        M, K = A.shape
     K2, N = B.shape
-    if K2 != K or tuple(C.shape) != (M, N):
+    if K2 != K or C.shape != (M, N):
         raise ValueError(f"shape mismatch A{tuple(A.shape)} B{tuple(B.shape)} C{tuple(C.shape)}")
-    return M, N, K, dtype_code(A.dtype) | (A_KMAJOR if a_kmajor else 0)
+    return M, N, K, (F32 if dt is torch.float32 else BF16) | (A_KMAJOR if a_kmajor else 0)
 
 
 def gemm_run(cfg, A, B, C, stream=None, a_kmajor=False):
