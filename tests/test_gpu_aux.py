@@ -75,3 +75,18 @@ def test_reference_product_at_tile_edges(gt, orc, shape, dtype, kmajor):
     C = torch.full((M, N), float("nan"), device="cuda")
     gt.gt_reference_gemm(Ad, B.cuda(), C, a_kmajor=kmajor)
     assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (1, 3), (3, 5), (4, 64), (5, 255), (3, 1025)])
+def test_split_k_clears_exactly_c(gt, rows, cols, offset):
+    """C full of NaN at every 4-byte alignment, sizes with every remainder
+    mod 4: a split-K product clears and fills C and nothing around it."""
+    K = 16
+    cfg = ((rows, 1, 1, 1), (2, 2, 1, 4), (cols, 1, 1, 1), 0)
+    A, B = torch.ones(rows, K, device="cuda"), torch.ones(K, cols, device="cuda")
+    buf = torch.full((rows * cols + 16,), float("nan"), device="cuda")
+    C = buf[4 + offset:4 + offset + rows * cols].view(rows, cols)
+    gt.gemm_run(cfg, A, B, C)
+    assert (C == K).all()
+    assert int(torch.isnan(buf).sum()) == 16
