@@ -42,7 +42,7 @@ __device__ __forceinline__ float load_in(const void* p, int64_t i, int dtype) {
 // Bound by fp32 VALU issue (one FMA per lane and 4 cycles without packed
 // instructions, 78.6 TFLOP/s): R·R FMAs against 2·R LDS values per k. 4096³
 // bf16: 42.6 ms with one thread per output reading A and B through the
-// caches, 1.75 ms (78 TFLOP/s) with 128×128 tiles; 1024³ 0.47 -> 0.10 ms. Rows,
+// caches, 1.75 ms (78 TFLOP/s) with 128×128 tiles; 1024³ 0.47 -> 0.08 ms. Rows,
 // columns and k past the edges are clamped for the loads (any size, any
 // alignment, scalar coalesced loads: 2·T·KC of them per T·T·KC FMAs) and
 // their products are not formed (k) or not stored (rows, columns).
@@ -218,8 +218,12 @@ namespace {
 template <int DT, bool AK>
 void launch_reference_tiled(const void* A, const void* B, float* C, int64_t M, int64_t N, int64_t K,
                             hipStream_t s) {
-  // The largest tile that leaves a workgroup or more for each of the 256
-  // compute units, else the smallest.
+  // The largest tile that gives more than one workgroup for most of the 256
+  // compute units, else the smallest: one workgroup alone on a CU is one
+  // wavefront a SIMD, which waits for LDS. 256 tiles against four times as many
+  // of half the size: 1024³ 107 and 79 µs, 2048³ 365 and 290 µs; 418 tiles
+  // (1360×1200×720) 78 and 91 µs.
+  constexpr int64_t kEnough = 384;
   const auto tiles = [&](int64_t t) { return (M + t - 1) / t * ((N + t - 1) / t); };
   const auto run = [&](auto tag) {
     constexpr int T = decltype(tag)::value;
@@ -228,9 +232,9 @@ void launch_reference_tiled(const void* A, const void* B, float* C, int64_t M, i
     hipLaunchKernelGGL((reference_kernel<DT, AK, T>), grid, dim3(256), 0, s, A, B, C, M, N, K,
                        (N + T - 1) / T, nt);
   };
-  if (tiles(128) >= 256)
+  if (tiles(128) >= kEnough)
     run(std::integral_constant<int, 128>{});
-  else if (tiles(64) >= 256)
+  else if (tiles(64) >= kEnough)
     run(std::integral_constant<int, 64>{});
   else
     run(std::integral_constant<int, 32>{});

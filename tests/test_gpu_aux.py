@@ -55,11 +55,12 @@ def test_compare_at_block_and_alignment_edges(gt, n, offsets):
                 assert got == want or (math.isnan(got) and math.isnan(want)), (where, side, value)
 
 
-# tile edges of each tile size (32, 64 and 128 outputs a side; 256 tiles or
+# tile edges of each tile size (32, 64 and 128 outputs a side; 384 tiles or
 # more pick the larger), one row or column past them, and K around a chunk of
 # 16 and below it
-REFERENCE = [(1, 1, 1), (31, 33, 15), (32, 32, 16), (33, 31, 17), (65, 1, 33), (1024, 1024, 5),
-             (993, 1025, 19), (1025, 993, 16), (2048, 2048, 3), (2049, 1921, 18), (1921, 2049, 1)]
+REFERENCE = [(1, 1, 1), (31, 33, 15), (32, 32, 16), (33, 31, 17), (65, 1, 33),
+             (1024, 1536, 5), (1024, 1472, 6), (1217, 1281, 19), (1281, 1217, 16),
+             (2048, 3072, 3), (2048, 2944, 2), (2433, 2561, 18), (2561, 2433, 1)]
 
 
 @pytest.mark.parametrize("kmajor", [False, True])
