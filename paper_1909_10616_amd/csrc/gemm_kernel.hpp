@@ -375,6 +375,15 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // per lane is then 256), 16 otherwise.
 constexpr int dl_inst_cap(int64_t acc) { return acc + 96 <= 256 ? 8 : 16; }
 
+// Whether the main loop writes a load's m0 ahead of the MFMA that the load
+// follows (ni: loads per wavefront and stage that the loop is built for, tiles:
+// MFMAs a chunk-step). With s_nop between two MFMAs instead, 256×256×32 tiles (32
+// MFMAs) lose 1 to 3 % (three boxes: 4096³ 112.2 against 111.2, 115.5 against
+// 112.7 µs, 2.08 M cycles a launch against 2.01 M; 4096×11008×4096 328 against 323,
+// 323 against 317 µs) and 16 MFMAs up to 0.5 %; with 2 and 4 the nop is the faster
+// (64×4096×4096 13.7 against 13.9 µs, 128×2624×3456 28.6 against 31.0 µs).
+constexpr bool dl_split(int ni, int tiles) { return ni > 0 && tiles >= 16; }
+
 // XOR applied to the 16-byte chunk index of B row k in LDS. A transposing
 // read touches rows k0 … k0+3 (k0 ≡ 0 mod 4) and, per 16-lane group, two
 // adjacent chunks (four per 32 lanes with 32×32 MFMA; with 16×16 MFMA the
@@ -430,7 +439,9 @@ __device__ __forceinline__ void wait_vm_at_most(int n) {
 // LDS byte address lds_base + 16·j. Written as inline assembly so that the
 // compiler does not see an LDS write it would have to wait for before every
 // LDS read (it cannot tell the ring slots apart); the ring's vmcnt accounting
-// is done explicitly.
+// is done explicitly. A load to LDS needs one wait state after a scalar write
+// of m0, which the compiler adds for its own loads but not inside an assembly
+// statement: s_nop 0 here, other instructions in the forms below.
 __device__ __forceinline__ void dma_load16(uint32_t off, uint64_t base, uint32_t lds_base) {
   // base and lds_base are uniform; reading them from the first lane keeps
   // them in scalar registers whatever the compiler inferred
@@ -439,16 +450,34 @@ __device__ __forceinline__ void dma_load16(uint32_t off, uint64_t base, uint32_t
       (static_cast<uint64_t>(static_cast<uint32_t>(
            __builtin_amdgcn_readfirstlane(static_cast<int>(base >> 32))))
        << 32);
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
                : "v"(off), "s"(sb), "s"(__builtin_amdgcn_readfirstlane(static_cast<int>(lds_base)))
                : "memory", "m0");
 }
 
+// The same in two parts with an MFMA between them, which is the wait state and
+// hides the write of m0. Nothing else in these kernels uses m0, which the
+// compiler reserves (checked on the disassembly).
+__device__ __forceinline__ void dma_set_lds(uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane(static_cast<int>(lds_base)))
+               : "memory", "m0");
+}
+__device__ __forceinline__ void dma_load16_set(uint32_t off, uint64_t base) {
+  const uint64_t sb =
+      static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)))) |
+      (static_cast<uint64_t>(static_cast<uint32_t>(
+           __builtin_amdgcn_readfirstlane(static_cast<int>(base >> 32))))
+       << 32);
+  asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(sb) : "memory");
+}
+
 // The same when n (a uniform value) is above i, and otherwise with no lane
 // enabled: the instruction then moves nothing but still counts in vmcnt. A
 // scalar select instead of a branch. (The instructions after the write of m0
-// also keep it the one wait state ahead of the load that the ISA asks for.)
+// are its wait state.)
 __device__ __forceinline__ void dma_load16_if(int n, int i, uint32_t off, uint64_t base,
                                               uint32_t lds_base) {
   asm volatile(
@@ -562,6 +591,12 @@ __device__ __forceinline__ void gemm_fast_dl(const KArgs& a, char* smem) {
     const uint32_t da = static_cast<uint32_t>(wave + i * nw) * 1024u;
     const uint32_t db = static_cast<uint32_t>(achunks + ((wave + (i - na_w) * nw) << 6)) * 16u;
     dma_load16(doff[i], isa ? ga : gb, sbase + (isa ? da : db));
+  };
+  // where instruction i writes (dma's lds_base)
+  auto dma_lds = [&](uint32_t sbase, int i) __attribute__((always_inline)) {
+    const uint32_t da = static_cast<uint32_t>(wave + i * nw) * 1024u;
+    const uint32_t db = static_cast<uint32_t>(achunks + ((wave + (i - na_w) * nw) << 6)) * 16u;
+    return sbase + (i < na_w ? da : db);
   };
   // Uniform origins of stage l's A and B tiles and LDS byte base of ring slot `slot`.
   struct StageBase {
@@ -727,8 +762,24 @@ __device__ __forceinline__ void gemm_fast_dl(const KArgs& a, char* smem) {
         load_frags(as, cs + 1, (cs + 1) & 1);
 #pragma unroll
         for (int q = 0; q < TMTN; ++q) {
-          mfma1(cs & 1, q);
-          dma_at(sbs, load, TMTN + cs * TMTN + q, open);
+          if constexpr (dl_split(NI, TMTN) && OPEN) {
+            const int pos = TMTN + cs * TMTN + q, i = pos / R;
+            if (pos % R == R - 1 && i < NIE && pos + 1 < SPOS) {
+              __builtin_amdgcn_sched_barrier(0);
+              dma_set_lds(dma_lds(sbs.sb, i));
+              __builtin_amdgcn_sched_barrier(0);
+              mfma1(cs & 1, q);
+              __builtin_amdgcn_sched_barrier(0);
+              dma_load16_set(doff[i], i < na_w ? sbs.ga : sbs.gb);
+              __builtin_amdgcn_sched_barrier(0);
+            } else {
+              mfma1(cs & 1, q);
+              dma_at(sbs, load, pos, open);
+            }
+          } else {
+            mfma1(cs & 1, q);
+            dma_at(sbs, load, TMTN + cs * TMTN + q, open);
+          }
         }
       }
       const bool more = OPEN || l + 1 < a.kLoop;
@@ -749,8 +800,24 @@ __device__ __forceinline__ void gemm_fast_dl(const KArgs& a, char* smem) {
       if (load2) sb2 = StageBase{ga2, gb2, cur_b};
 #pragma unroll
       for (int q = 0; q < TMTN; ++q) {
-        mfma1((NCS - 1) & 1, q);
-        dma_at(sb2, load2, q, open);
+        if constexpr (dl_split(NI, TMTN) && OPEN) {
+          const int i = q / R;
+          if (q % R == R - 1 && i < NIE && q + 1 < SPOS) {
+            __builtin_amdgcn_sched_barrier(0);
+            dma_set_lds(dma_lds(sb2.sb, i));
+            __builtin_amdgcn_sched_barrier(0);
+            mfma1((NCS - 1) & 1, q);
+            __builtin_amdgcn_sched_barrier(0);
+            dma_load16_set(doff[i], i < na_w ? sb2.ga : sb2.gb);
+            __builtin_amdgcn_sched_barrier(0);
+          } else {
+            mfma1((NCS - 1) & 1, q);
+            dma_at(sb2, load2, q, open);
+          }
+        } else {
+          mfma1((NCS - 1) & 1, q);
+          dma_at(sb2, load2, q, open);
+        }
       }
       if constexpr (NCS == 1) {
         if (more) load_frags(nx, 0, 0);
