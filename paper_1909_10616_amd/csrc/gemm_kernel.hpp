@@ -940,6 +940,77 @@ constexpr bool ring_needs(int nh) {
   return false;
 }
 
+// Whether the accumulators, the fragments of two chunk-steps and their offsets
+// (9 registers a tile row and column) and some 80 for the loads and addresses
+// pass what the launch bound gives a lane (256, or 512 for kernels of at most 4
+// wavefronts): then a chunk-step holds the fragments of the shorter side of
+// the wavefront's tile and a few of the longer one's, read that many tiles ahead
+// (ring_stream_step). (16×16 MFMA; no tile of 32×32 ones spills. Not 4×16 and
+// 16×4 fp32 tiles in 64-deep stages, which fit without: the compiler then moves
+// their 256 accumulators about, 440 against 298 µs at 2048×2048×1024.)
+template <int DT, int I, int TM, int TN, int CPR>
+constexpr bool ring_streams() {
+  constexpr int acc = TM * TN * I * I / 64, spare = DT == 0 && CPR == 16 && acc == 256 ? 32 : 80;
+  return I == 16 && acc + 9 * (TM + TN) + spare > (acc + 96 > 256 ? 512 : 256);
+}
+
+// One chunk-step of such a kernel: fragments from the stage at st, MFMAs in the
+// order of the longer side's tiles, between(g) after each quarter of them.
+template <int DT, int I, int TM, int TN, int CPR, bool AK, typename acc_t, typename F>
+__device__ __forceinline__ void ring_stream_step(acc_t (&acc)[TM][TN], const char* st, int cs,
+                                                 const uint32_t (&xa)[TM], const uint32_t (&xb)[TN],
+                                                 int af, int plane, F between) {
+  constexpr int G = 64 / I, WM = TM * I, WN = TN * I;
+  constexpr bool PLANES = DT == 1 && I == 16 && CPR / G >= 2;
+  constexpr bool BL = TN >= TM;  // B's side is the longer one
+  constexpr int S = BL ? TM : TN, L = BL ? TN : TM;
+  constexpr int D = S >= 4 ? 4 : 8;  // tiles of the longer side read ahead
+  static_assert(L >= D, "a streamed tile has a long side");
+  auto read = [&](bool b, int t) __attribute__((always_inline)) {
+    u32x4 v;
+    if (b && DT == 1) {
+      s16x4 h[2];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+        h[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4*)(st + xb[t] + (cs * G * 8 + 4 * hh) * WN * 2));
+      v = __builtin_bit_cast(u32x4, __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+    } else if (b || AK) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        v[q] = *reinterpret_cast<const unsigned*>(st + (b ? xb[t] : xa[t]) + (cs * G * 4 + q) * (b ? WN : WM) * 4);
+    } else if (PLANES) {
+      v = *reinterpret_cast<const u32x4*>(st + cs * plane + xa[t]);
+    } else {
+      v = *reinterpret_cast<const u32x4*>(st + xa[t] + ((af ^ (cs * G)) << 4));
+    }
+    return v;
+  };
+  u32x4 fs[S], fl[D];
+#pragma unroll
+  for (int t = 0; t < S; ++t) fs[t] = read(!BL, t);
+#pragma unroll
+  for (int t = 0; t < D; ++t) fl[t] = read(BL, t);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 0; t < L; ++t) {
+#pragma unroll
+    for (int q = 0; q < (DT == 1 ? 1 : 4); ++q)
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const u32x4 va = BL ? fs[s] : fl[t % D], vb = BL ? fl[t % D] : fs[s];
+        acc_t& c = acc[BL ? s : t][BL ? t : s];
+        if constexpr (DT == 1)
+          c = mfma_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, vb), c);
+        else
+          c = mfma_f32(__builtin_bit_cast(f32x4, va)[q], __builtin_bit_cast(f32x4, vb)[q], c);
+      }
+    if (t + D < L) fl[t % D] = read(BL, t + D);
+    if ((t + 1) % (L / 4) == 0) between((t + 1) / (L / 4) - 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 template <int DT, int I, int TM, int TN, int CPR, bool AK>
 __device__ __forceinline__ void gemm_ring(const KArgs& a, char* smem) {
   static_assert(DT == 0 || !AK, "the K-major-A ring is fp32 only");
@@ -1149,14 +1220,20 @@ __device__ __forceinline__ void gemm_ring(const KArgs& a, char* smem) {
       issue_all(ga, gb, lds0);
       waitcnt_vm<0>();
       ring_barrier();
-      load_frags(smem, 0, 0);
+      if constexpr (ring_streams<DT, I, TM, TN, CPR>()) {
 #pragma unroll
-      for (int cs = 0; cs < NCS; ++cs) {
-        if (cs + 1 < NCS) load_frags(smem, cs + 1, (cs + 1) & 1);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int cs = 0; cs < NCS; ++cs)
+          ring_stream_step<DT, I, TM, TN, CPR, AK>(acc, smem, cs, xa, xb, af, plane, [](int) {});
+      } else {
+        load_frags(smem, 0, 0);
 #pragma unroll
-        for (int g = 0; g < SG; ++g) mfmas(cs & 1, g);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int cs = 0; cs < NCS; ++cs) {
+          if (cs + 1 < NCS) load_frags(smem, cs + 1, (cs + 1) & 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int g = 0; g < SG; ++g) mfmas(cs & 1, g);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       waitcnt_lgkm0();
       ring_barrier();
@@ -1228,44 +1305,64 @@ __device__ __forceinline__ void gemm_ring(const KArgs& a, char* smem) {
       }
       wait_stage(-1);
       ring_barrier();
-      w = window(orgA + static_cast<uint64_t>(ns - 1) * stepA, orgB + static_cast<uint64_t>(ns - 1) * stepB,
-                 lds0 + (ns - 1) * stage16, ns - 1 < kLoop);
-      load_frags(smem, 0, 0);
+      if constexpr (ring_streams<DT, I, TM, TN, CPR>()) {
+        // The boundary comes after a stage's last chunk-step, and the loads of
+        // stage l + ns − 1, into the slot of stage l − 1, are issued during stage l.
+        uint32_t cur_b = 0, free_b = ring - stage16;
+        for (int l = 0; l < kLoop; ++l) {
+          w = window(w.ga + stepA, w.gb + stepB, lds0 + free_b, l + ns - 1 < kLoop);
 #pragma unroll
-      for (int g = 0; g < SG; ++g) group(w, g);
-      uint32_t cur_b = 0;  // this stage's slot, bytes from the ring's start
-      for (int l = 0; l < kLoop; ++l) {
-        const char* st = smem + cur_b;
-        const uint32_t nx_b = cur_b + stage16 == ring ? 0u : cur_b + stage16;
+          for (int cs = 0; cs < NCS; ++cs)
+            ring_stream_step<DT, I, TM, TN, CPR, AK>(acc, smem + cur_b, cs, xa, xb, af, plane,
+                                                     [&](int g) __attribute__((always_inline)) { group(w, SG * cs + g); });
+          waitcnt_lgkm0();
+          if (l + 1 < kLoop) {
+            wait_stage(l);
+            ring_barrier();
+          }
+          free_b = cur_b;
+          cur_b = cur_b + stage16 == ring ? 0u : cur_b + stage16;
+        }
+      } else {
+        w = window(orgA + static_cast<uint64_t>(ns - 1) * stepA, orgB + static_cast<uint64_t>(ns - 1) * stepB,
+                   lds0 + (ns - 1) * stage16, ns - 1 < kLoop);
+        load_frags(smem, 0, 0);
 #pragma unroll
-        for (int cs = 0; cs + 1 < NCS; ++cs) {
-          load_frags(st, cs + 1, (cs + 1) & 1);
-          __builtin_amdgcn_sched_barrier(0);
+        for (int g = 0; g < SG; ++g) group(w, g);
+        uint32_t cur_b = 0;  // this stage's slot, bytes from the ring's start
+        for (int l = 0; l < kLoop; ++l) {
+          const char* st = smem + cur_b;
+          const uint32_t nx_b = cur_b + stage16 == ring ? 0u : cur_b + stage16;
+#pragma unroll
+          for (int cs = 0; cs + 1 < NCS; ++cs) {
+            load_frags(st, cs + 1, (cs + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < SG; ++g) {
+              mfmas(cs & 1, g);
+              group(w, SG + SG * cs + g);
+            }
+          }
+          const bool more = l + 1 < kLoop;
+          // (outside the branch: past it the compiler would wait for the next
+          // stage's fragments too)
+          waitcnt_lgkm0();
+          if (more) {
+            wait_stage(l);
+            ring_barrier();
+            if constexpr (NCS >= 2) load_frags(smem + nx_b, 0, 0);
+          }
+          w = window(w.ga + stepA, w.gb + stepB, lds0 + cur_b, l + ns < kLoop);
 #pragma unroll
           for (int g = 0; g < SG; ++g) {
-            mfmas(cs & 1, g);
-            group(w, SG + SG * cs + g);
+            mfmas((NCS - 1) & 1, g);
+            group(w, g);
           }
+          if constexpr (NCS == 1) {
+            if (more) load_frags(smem + nx_b, 0, 0);
+          }
+          cur_b = nx_b;
         }
-        const bool more = l + 1 < kLoop;
-        // (outside the branch: past it the compiler would wait for the next
-        // stage's fragments too)
-        waitcnt_lgkm0();
-        if (more) {
-          wait_stage(l);
-          ring_barrier();
-          if constexpr (NCS >= 2) load_frags(smem + nx_b, 0, 0);
-        }
-        w = window(w.ga + stepA, w.gb + stepB, lds0 + cur_b, l + ns < kLoop);
-#pragma unroll
-        for (int g = 0; g < SG; ++g) {
-          mfmas((NCS - 1) & 1, g);
-          group(w, g);
-        }
-        if constexpr (NCS == 1) {
-          if (more) load_frags(smem + nx_b, 0, 0);
-        }
-        cur_b = nx_b;
       }
     };
     // The most loads of one operand that any wavefront of the workgroup has.

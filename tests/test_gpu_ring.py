@@ -64,6 +64,16 @@ BF16 = [
     ((2, 1, 1, 16), (1, 1, 64, 16), (3, 1, 1, 32), 16),      # … of 1024
     *[((2, 8, 1, 16), (2, 1, 1, 32), (k, 4, 1, 32), 16) for k in (1, 2, 5)],
 ]
+# wavefront tiles whose fragments are streamed, one wavefront and more, K of one
+# to many stages, every stage depth
+WIDE = [((1, 1, tm, 16), (2, 1, tn, 16), (k, 1, 1, d))
+        for tm, tn in ((1, 16), (16, 1), (1, 32), (32, 1), (2, 16), (16, 2), (4, 8), (8, 4), (1, 64), (64, 1),
+                       (2, 32), (32, 2), (4, 16), (16, 4)) for k, d in ((1, 64), (2, 32), (3, 64), (7, 32))] + \
+       [((1, 4, 4, 16), (2, 2, 8, 16), (5, 1, 1, 64)), ((2, 2, 16, 16), (1, 4, 1, 16), (5, 1, 1, 32)),
+        ((1, 1, 2, 16), (1, 2, 32, 16), (9, 1, 1, 32)), ((2, 1, 32, 16), (1, 1, 1, 16), (3, 2, 1, 32))]
+CASES += [(m, n, (*k[:3], max(k[3] >> s, 16)), 0) for m, n, k in WIDE for s in (0, 1)
+          if (np.prod(m[1:]) + np.prod(n[1:])) * (k[3] >> s) * 4 <= 163840]
+BF16 += [(m, n, k, 16) for m, n, k in WIDE]
 ALL = [("f32", c, km) for c in CASES for km in (False, True)] + [("bf16", c, False) for c in BF16]
 
 

@@ -170,10 +170,11 @@ def test_reads_find_what_the_loads_wrote(bf16, ak):
                         assert (kk[w] == cs * G * 8 + (LANE // I) * 8 + 4 * hh + j).all()
 
 
-def replay(ns, kLoop, NCS, na, nb, most, SG):
+def replay(ns, kLoop, NCS, na, nb, most, SG, streams):
     """One wavefront's loads, waits, barriers and reads, in program order; a
     load that moves nothing is ("load", None). na, nb: its loads of A and B;
-    most: the most of either that any wavefront has."""
+    most: the most of either that any wavefront has; streams: the form that
+    reads a chunk-step's fragments while it multiplies them."""
     ev, cnt = [], na + nb
     if ns == 1:
         for l in range(kLoop):
@@ -202,6 +203,18 @@ def replay(ns, kLoop, NCS, na, nb, most, SG):
         group(window(l), -1)
     wait(-1)
     ev.append(("bar",))
+    if streams:
+        for l in range(kLoop):
+            st = window(l + ns - 1)
+            for cs in range(NCS):
+                ev.append(("read", l))
+                for g in range(SG):
+                    ev.append(("read", l))
+                    group(st, SG * cs + g)
+            if l + 1 < kLoop:
+                wait(l)
+                ev.append(("bar",))
+        return ev
     st = window(ns - 1)
     ev.append(("read", 0))
     for g in range(SG):
@@ -225,8 +238,9 @@ def replay(ns, kLoop, NCS, na, nb, most, SG):
     return ev
 
 
+@pytest.mark.parametrize("streams", [False, True])
 @pytest.mark.parametrize("ns", range(1, 9))
-def test_ring_order(ns):
+def test_ring_order(ns, streams):
     """Every load is issued once, into a slot whose stage every wavefront has
     read (a barrier between), and has landed, a barrier before its first
     read, for wavefronts with fewer loads than others too."""
@@ -235,7 +249,7 @@ def test_ring_order(ns):
         for na, nb in {(most, most), (most, 0), (0, most), (most - 1, most), (most, most // 2)}:
             cnt = na + nb
             issued, ready, last_read, bars, landed = [], set(), {}, 0, set()
-            for e in replay(ns, kLoop, NCS, na, nb, most, SG):
+            for e in replay(ns, kLoop, NCS, na, nb, most, SG, streams):
                 if e[0] == "load":
                     if e[1] is not None:
                         assert e[1] < kLoop
