@@ -50,7 +50,8 @@ struct KArgs {
   int32_t aKM;             // A given K-major (K×M row-major, element (m, k) at A[k·M + m])
   int32_t lgBM;
   int32_t stream;          // generic path: wavefronts read their own operands
-  int32_t wide;            // gemm_ring: a stage's offsets from its origins exceed 32 bits
+  int32_t wide;            // gemm_ring: a stage's offsets from its origins exceed 32 bits,
+                           // the loads step 64-bit addresses
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -474,7 +475,15 @@ __device__ __forceinline__ void dma_load16_set(uint32_t off, uint64_t base) {
   asm volatile("global_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(sb) : "memory");
 }
 
-// The same when n (a uniform value) is above i, and otherwise with no lane
+// The same from a 64-bit address of each lane's own.
+__device__ __forceinline__ void dma_load16_at(uint64_t addr, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(addr), "s"(__builtin_amdgcn_readfirstlane(static_cast<int>(lds_base)))
+               : "memory", "m0");
+}
+
+// dma_load16 when n (a uniform value) is above i, and otherwise with no lane
 // enabled: the instruction then moves nothing but still counts in vmcnt. A
 // scalar select instead of a branch. (The instructions after the write of m0
 // are its wait state.)
@@ -1110,16 +1119,59 @@ __device__ __forceinline__ void gemm_ring(const KArgs& a, char* smem) {
     p.dst += bbase;
     return p;
   };
-  // All of this wavefront's loads of a stage, back to back, at any distance.
+  // All of this wavefront's loads of a stage, back to back, at any distance:
+  // every lane steps a 64-bit address of its own. What changes from load to
+  // load is added up, not worked out from the load's number, which with 16 and
+  // more of them cost more than the stage's MFMAs. (The lane's number is made
+  // opaque, so that what follows from it is not kept in registers between
+  // stages: spilled, its reload waits for every load on its way.)
+  auto issue_panel = [&](const Share& h, uint64_t g, uint64_t ld, uint32_t slot, auto wtag, int insts) __attribute__((always_inline)) {
+    constexpr int C = decltype(wtag)::value / VEC;
+    constexpr int RI = C >= 64 ? 1 : 64 / C, IR = C >= 64 ? C / 64 : 1;  // rows an instruction, instructions a row
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    uint32_t dst = slot + static_cast<uint32_t>(h.block * insts + h.b0) * 1024u;
+    int b = h.b0, k = b / IR * RI + (C >= 64 ? 0 : ln / C);
+    uint64_t at = g + static_cast<uint64_t>(h.block * C) * 16u + static_cast<uint64_t>(k) * ld;
+    const uint64_t step = static_cast<uint64_t>(h.db * RI) * ld;
+    for (int j = 0; j < h.cnt; ++j) {
+      const int x = DT == 1 ? bswz(k, C) : (flip_panel<I, C>() ? k & 4 : 0);
+      const int pos = (C >= 64 ? b % IR * 64 + ln : ln % C) ^ x;
+      dma_load16_at(at + static_cast<uint64_t>(pos) * 16u, dst);
+      dst += static_cast<uint32_t>(h.db) * 1024u;
+      b += h.db;
+      if constexpr (IR == 1) {
+        k += h.db * RI;
+        at += step;
+      } else {
+        at += static_cast<uint64_t>(b / IR - k) * ld;
+        k = b / IR;
+      }
+    }
+  };
   auto issue_all = [&](uint64_t ga, uint64_t gb, uint32_t slot) __attribute__((always_inline)) {
-    for (int j = 0; j < ha.cnt; ++j) {
-      const Place p = place_a(j);
-      dma_load16_if(1, 0, p.lane, ga + p.at, slot + p.dst);
+    if constexpr (AK) {
+      issue_panel(ha, ga, lda, slot, std::integral_constant<int, WM>{}, NPA);
+    } else {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      uint32_t dst = slot + static_cast<uint32_t>(ha.b0) * 1024u;
+      int s = (ha.b0 << 6) + ln;
+      for (int j = 0; j < ha.cnt; ++j) {
+        if constexpr (PLANES) {
+          const int lgp = a.lgBM + 2, q = swz(s & ((1 << lgp) - 1));  // slots per plane: 4·BM
+          dma_load16_at(ga + static_cast<uint64_t>(q >> 2) * lda + static_cast<uint64_t>(s >> lgp) * 64u +
+                            static_cast<uint64_t>(q & 3) * 16u, dst);
+        } else {
+          const int row = s >> LGCPR;
+          dma_load16_at(ga + static_cast<uint64_t>(row) * lda +
+                            static_cast<uint64_t>((s & (CPR - 1)) ^ fswz<CPR>(row)) * 16u, dst);
+        }
+        s += ha.db << 6;
+        dst += static_cast<uint32_t>(ha.db) * 1024u;
+      }
     }
-    for (int j = 0; j < hb.cnt; ++j) {
-      const Place p = place_b(j);
-      dma_load16_if(1, 0, p.lane, gb + p.at, slot + p.dst);
-    }
+    issue_panel(hb, gb, ldb, slot + bbase, std::integral_constant<int, WN>{}, NPB);
   };
 
   acc_t acc[TM][TN];

@@ -112,17 +112,11 @@ int lower(const gt_config& c, int64_t M, int64_t N, int64_t K, int dtype, const 
   const int G = 64 / L.I;
   const int64_t cpr = L.BK / vec;  // 16-byte chunks per LDS row
   const bool cpr_ok = L.BK % vec == 0 && (cpr == 2 || cpr == 4 || cpr == 8 || cpr == 16);
-  // (a K-major A needs 16-byte m chunks, M % vec; its fast path is fp32 only;
-  // the ring's loads keep 32-bit offsets over the rows of one instruction, 64
-  // chunks of a tile or panel)
-  const int64_t rows_a = std::max<int64_t>(
-      akm ? 64 * vec / std::max<int64_t>(L.repM * L.blkM, 1) : 64 / std::max<int64_t>(cpr, 1), 16);
-  const int64_t rows_b = std::max<int64_t>(64 * vec / std::max<int64_t>(L.repN * L.blkN, 1), 1);
+  // (a K-major A needs 16-byte m chunks, M % vec; its fast path is fp32 only)
   const bool fast = L.blkM % L.I == 0 && L.blkN % L.I == 0 && L.kBlk % L.IK == 0 &&
                     L.BK % (vec * G) == 0 && cpr_ok && L.BN % vec == 0 && K % vec == 0 &&
                     N % vec == 0 && L.W <= 8 && aligned16(A) && aligned16(B) &&
-                    (!akm || (dt == GT_F32 && L.BM % vec == 0 && M % vec == 0)) &&
-                    std::max(rows_a * (akm ? M : K), rows_b * N) * L.elem < (int64_t{1} << 32);
+                    (!akm || (dt == GT_F32 && L.BM % vec == 0 && M % vec == 0));
   const int64_t stage_bytes = (L.BM * L.BK + L.BK * L.BN) * L.elem;
   const bool dbuf = L.kLoop >= 2 && 2 * stage_bytes <= kLdsMax;
   // bf16 fast path with direct global->LDS loads into a ring of ns stages:

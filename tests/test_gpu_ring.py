@@ -106,3 +106,44 @@ def test_offsets_past_32_bits(gt):
     gt.gemm_run(cfg, A, B, C)
     gt.gt_reference_gemm(A, B, R)
     assert torch.equal(C, R)
+
+
+def _small_integers(shape, seed):
+    """Entries in {-1, 0, 1}, drawn in pieces."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    out = torch.empty(shape, device="cuda")
+    flat = out.view(-1)
+    for i in range(0, flat.numel(), 1 << 28):
+        n = min(1 << 28, flat.numel() - i)
+        flat[i:i + n] = torch.randint(-1, 2, (n,), generator=g, device="cuda", dtype=torch.int8)
+    return out
+
+
+def test_rows_of_one_load_past_32_bits(gt):
+    """An instruction that covers 32 rows of an A with 2^28-byte rows (8 GiB):
+    its lanes lie further than 2^32 bytes apart. The sums of the slices, in
+    {-1, 0, 1} products, are exact in any order."""
+    M, N, K = 32, 32, 1 << 26
+    A, B = _small_integers((M, K), 5), _small_integers((K, N), 6)
+    cfg = ((1, 1, 1, 32), (K // 8 // 256, 256, 1, 8), (1, 1, 1, 32), 0)
+    info = gt.lower(cfg, M, N, K, "f32")
+    assert info["fast"] == 1 and info["ring"] >= 2
+    C = torch.full((M, N), float("nan"), device="cuda")
+    gt.gemm_run(cfg, A, B, C)
+    R = torch.zeros(M, N, device="cuda", dtype=torch.float64)
+    for k in range(0, K, 1 << 22):
+        R += torch.mm(A[:, k:k + (1 << 22)].contiguous(), B[k:k + (1 << 22)]).double()
+    assert torch.equal(C.double(), R)
+
+
+def test_rows_of_one_panel_load_past_32_bits(gt):
+    """The same of a B with 2^29-byte rows (16 GiB), 16 of them an instruction."""
+    M, N, K = 16, 1 << 27, 32
+    A, B = _small_integers((M, K), 7), _small_integers((K, N), 8)
+    cfg = ((1, 1, 1, 16), (2, 1, 1, 16), (N // 16, 1, 1, 16), 0)
+    info = gt.lower(cfg, M, N, K, "f32")
+    assert info["fast"] == 1 and info["ring"] == 2
+    C, R = torch.full((M, N), float("nan"), device="cuda"), torch.empty(M, N, device="cuda")
+    gt.gemm_run(cfg, A, B, C)
+    gt.gt_reference_gemm(A, B, R)
+    assert torch.equal(C, R)

@@ -310,12 +310,59 @@ def test_lowered_launches_stay_in_bounds(gt, space, dt, akm):
     assert seen >= 80, (seen, tries)
 
 
-@pytest.mark.parametrize("dt,dims,fast", [
-    ("f32", (256, 256, 1 << 25), 1), ("f32", (256, 256, 1 << 26), 0),
-    ("f32", (256, 1 << 26, 256), 1), ("f32", (256, 1 << 27, 256), 0),
-    ("bf16", (256, 256, 1 << 26), 1), ("bf16", (256, 256, 1 << 27), 0)])
-def test_extents_whose_lane_offsets_would_wrap_take_the_generic_path(gt, dt, dims, fast):
-    """16 rows of A, or the 8 rows of a 32-column fp32 panel, past 2^32 bytes."""
+@pytest.mark.parametrize("dt,dims", [
+    ("f32", (256, 256, 1 << 25)), ("f32", (256, 256, 1 << 26)), ("f32", (256, 1 << 26, 256)),
+    ("f32", (256, 1 << 27, 256)), ("bf16", (256, 256, 1 << 26)), ("bf16", (256, 256, 1 << 27))])
+def test_extents_whose_lane_offsets_would_wrap_stay_on_the_ring(gt, dt, dims):
+    """16 rows of A, or the 8 rows of a 32-column fp32 panel, reach 2^32 bytes:
+    the loads there step a 64-bit address per lane, so no extent leaves the
+    fast path."""
     M, N, K = dims
     cfg = ((M // 64, 2, 1, 32), (K // 32, 1, 1, 32), (N // 64, 2, 1, 32), 32 if dt == "bf16" else 0)
-    assert gt.lower(cfg, M, N, K, dt)["fast"] == fast
+    info = gt.lower(cfg, M, N, K, dt)
+    assert info["fast"] == 1 and info["ring"] >= 2
+
+
+@pytest.mark.parametrize("bf16,ak", [(False, False), (False, True), (True, False)])
+def test_stepped_loads_equal_the_numbered_ones(bf16, ak):
+    """The loads issued at once add a step from one to the next; here their
+    places are worked out by the same steps and compared with each load's own."""
+    vec = 8 if bf16 else 4
+    ld = 1 << 36       # rows far beyond 32 bits
+    for I, TM, TN, cpr in SHAPES:
+        BK = cpr * vec
+        for wavesM, wavesN in ((1, 1), (2, 1), (1, 2), (4, 2)):
+            nw, BM = wavesM * wavesN, wavesM * TM * I
+            for w in range(nw):
+                for panels, W, ww in ((wavesN, TN * I, nw - 1 - w),) + (((wavesM, TM * I, w),) if ak else ()):
+                    C = W // vec
+                    RI, IR = max(64 // C, 1), max(C // 64, 1)
+                    panel, bs = share(ww, nw, panels, BK * C // 64)
+                    db, b, got = nw // panels, ww // panels, []
+                    k = b // IR * RI + (LANE * 0 if C >= 64 else LANE // C)
+                    at = panel * W + k * ld
+                    for _ in bs:
+                        x = np.array([bswz(int(v), C) for v in k]) if bf16 else (k & 4 if flip_panel(I, C) else 0 * k)
+                        pos = (b % IR * 64 + LANE if C >= 64 else LANE % C) ^ x
+                        got.append((panel * (BK * C // 64) + b, at + pos * vec))
+                        b += db
+                        at = at + (db * RI * ld if IR == 1 else (b // IR - k) * ld)
+                        k = k + db * RI if IR == 1 else 0 * k + b // IR
+                    want = panel_loads(ww, nw, panels, I, W, BK, ld, bf16)
+                    assert [g[0] for g in got] == [g[0] for g in want]
+                    assert all((g[1] == v[1]).all() for g, v in zip(got, want))
+                if not ak:
+                    b, got = w, []
+                    s = (b << 6) + LANE
+                    for _ in share(w, nw, 1, BM * cpr >> 6)[1]:
+                        if planes(bf16, I, cpr):
+                            q = swz(s % (4 * BM))
+                            off = (q >> 2) * ld + s // (4 * BM) * 4 * vec + (q & 3) * vec
+                        else:
+                            row = s // cpr
+                            off = row * ld + ((s % cpr) ^ fswz(row, cpr)) * vec
+                        got.append((b, off))
+                        b, s = b + nw, s + (nw << 6)
+                    want = row_loads(w, nw, BM, cpr, ld, bf16, I)
+                    assert [g[0] for g in got] == [g[0] for g in want]
+                    assert all((g[1] == v[1]).all() for g, v in zip(got, want))
