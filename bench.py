@@ -56,11 +56,10 @@ def kernel_name(w, info):
     """Symbol of the kernel instantiation a lowered configuration launches."""
     dt = 1 if w.dtype == "bf16" else 0
     cpr = info["BK"] // (8 if w.dtype == "bf16" else 4) if info["fast"] else 0
-    # direct loads per wavefront and stage: the counts gemm_kernel_dl takes
-    cap = 8 if info["acc_regs"] + 96 <= 256 else 16
-    per_wave = (info["BM"] + info["BN"]) * info["BK"] // 512 // info["waves"]
-    if info["dl"] and (per_wave in (cap, cap // 2) or per_wave <= 3):
+    if info["kernel"] == "even":
         return f"gt::gemm_kernel_dl<{info['I']}, {info['TM']}, {info['TN']}, {cpr}>"
+    if info["kernel"] == "stream":   # (A is row-major in every workload)
+        return f"gt::gemm_kernel_stream<{dt}, {info['I']}, {info['TM']}, {info['TN']}, false>"
     return f"gt::gemm_kernel<{dt}, {info['I']}, {info['TM']}, {info['TN']}, {cpr}>"
 
 

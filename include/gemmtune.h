@@ -203,6 +203,15 @@ typedef struct gt_kernel_info {
 int gt_lower(const gt_config* cfg, int64_t M, int64_t N, int64_t K, int dtype,
              gt_kernel_info* info);
 
+/* Which kernel that is: of the generic path (fast 0) the one with shared
+ * stages or the one whose wavefronts read their own operands, of the fast path
+ * the general ring or the bf16 ring with evenly shared loads. Arguments and
+ * errors as gt_lower's. */
+enum gt_kernel { GT_KERNEL_GENERIC = 0, GT_KERNEL_STREAM = 1, GT_KERNEL_RING = 2,
+                 GT_KERNEL_EVEN = 3 };
+int gt_lower_kernel(const gt_config* cfg, int64_t M, int64_t N, int64_t K, int dtype,
+                    int* kernel);
+
 /* ---- G-BFS (§4.2, Alg.1) ---------------------------------------------- */
 
 /* Per-timed-configuration log record. status: 0 ok, 1 early abort,

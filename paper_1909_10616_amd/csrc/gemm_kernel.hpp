@@ -44,8 +44,8 @@ struct KArgs {
   int32_t atomic;          // split-K: accumulate with fp32 atomics
   int32_t remap;           // XCD-aware workgroup order
   int32_t aVec, bVec;      // generic path: 1 or 16-byte vector tile loads
-  int32_t dl;              // bf16 fast path: loads in whole equal shares (gemm_fast_dl's shape)
-  int32_t dlk;             // … that gemm_fast_dl itself takes
+  int32_t dl;              // bf16 fast path: loads in whole equal shares (reported only)
+  int32_t dlk;             // … that gemm_fast_dl takes
   int32_t ns;              // ring stages (fast path)
   int32_t aKM;             // A given K-major (K×M row-major, element (m, k) at A[k·M + m])
   int32_t lgBM;
@@ -484,8 +484,10 @@ __device__ __forceinline__ void dma_load16_at(uint64_t addr, uint32_t lds_base) 
 }
 
 // dma_load16 when n (a uniform value) is above i, and otherwise with no lane
-// enabled: the instruction then moves nothing but still counts in vmcnt. A
-// scalar select instead of a branch. (The instructions after the write of m0
+// enabled: the instruction then moves nothing but still counts in vmcnt, in its
+// place in the order (measured: after one load of cold memory and eight masked
+// ones, vmcnt(8) waited for the first in each of 4096 wavefronts). A scalar
+// select instead of a branch. (The instructions after the write of m0
 // are its wait state.)
 __device__ __forceinline__ void dma_load16_if(int n, int i, uint32_t off, uint64_t base,
                                               uint32_t lds_base) {
@@ -635,8 +637,9 @@ __device__ __forceinline__ void gemm_fast_dl(const KArgs& a, char* smem) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{};
 
-  // A fragment slots: in the [m][k] layout as in the register-staged path;
-  // in the plane layout, this lane's slot in plane 0 (plane cs adds 4·BM·cs).
+  // A fragment slots: in the [m][k] layout a per-row base, to which a
+  // chunk-step adds its XOR and line; in the plane layout, this lane's slot in
+  // plane 0 (plane cs adds 4·BM·cs).
   const int grp = lane / I;
   int xa[TM][NLINE];
 #pragma unroll
@@ -1749,8 +1752,8 @@ __global__ void __launch_bounds__((launch_threads<I, TM, TN, CPR>())) gemm_kerne
   gemm_ring<0, I, TM, TN, CPR, true>(a, reinterpret_cast<char*>(gt_smem));
 }
 
-// bf16 fast path with direct global→LDS loads: a kernel of its own, so that
-// its register allocation does not inherit the register-staged path's.
+// bf16 fast path with evenly shared loads: a kernel of its own, so that its
+// register allocation does not inherit the general ring's.
 template <int I, int TM, int TN, int CPR>
 __global__ void __launch_bounds__((launch_threads<I, TM, TN, CPR>())) gemm_kernel_dl(KArgs a) {
   extern __shared__ u32x4 gt_smem[];

@@ -468,4 +468,18 @@ int gt_lower(const gt_config* cfg, int64_t M, int64_t N, int64_t K, int dtype,
   return GT_OK;
 }
 
+int gt_lower_kernel(const gt_config* cfg, int64_t M, int64_t N, int64_t K, int dtype,
+                    int* kernel) {
+  if (!cfg || !kernel) {
+    gt::set_error("gt_lower_kernel: null argument");
+    return GT_EINVAL;
+  }
+  gt::Lowered lw;  // the view gt_lower gives
+  static const uint4 dummy[1] = {};
+  if (int rc = gt::lower(*cfg, M, N, K, dtype, dummy, dummy, nullptr, &lw)) return rc;
+  *kernel = lw.fast ? (lw.args.dlk ? GT_KERNEL_EVEN : GT_KERNEL_RING)
+                    : (lw.args.stream ? GT_KERNEL_STREAM : GT_KERNEL_GENERIC);
+  return GT_OK;
+}
+
 }  // extern "C"

@@ -95,8 +95,10 @@ class gt_tune_result(ctypes.Structure):
 
 EXPORTS = ("gt_space_size", "enumerate_configs", "config_rank", "config_unrank", "config_legit",
            "neighbours", "gemm_run", "gt_measure", "gt_reference_gemm", "gt_compare",
-           "gt_lower", "gt_tune_opts_init", "tune_gbfs", "tune_random", "gt_na2c_params_init",
-           "tune_na2c", "gt_shutdown", "gt_compare_noalloc", "gt_last_error")
+           "gt_lower", "gt_lower_kernel", "gt_tune_opts_init", "tune_gbfs", "tune_random",
+           "gt_na2c_params_init", "tune_na2c", "gt_shutdown", "gt_compare_noalloc",
+           "gt_last_error")
+KERNELS = ("generic", "stream", "ring", "even")   # gt_lower_kernel's values
 
 _lib = None
 
@@ -131,6 +133,7 @@ def lib():
     L.gt_reference_gemm.argtypes = [P, P, P, i64, i64, i64, i32, P]
     L.gt_compare.argtypes = [P, P, i64, P, ctypes.POINTER(ctypes.c_double)]
     L.gt_lower.argtypes = [CF, i64, i64, i64, i32, ctypes.POINTER(gt_kernel_info)]
+    L.gt_lower_kernel.argtypes = [CF, i64, i64, i64, i32, ctypes.POINTER(i32)]
     L.gt_tune_opts_init.argtypes = [ctypes.POINTER(gt_tune_opts)]
     L.tune_gbfs.argtypes = [SP, ctypes.POINTER(gt_tune_opts), gt_cost_fn, P,
                             ctypes.POINTER(gt_tune_result)]
@@ -268,7 +271,11 @@ def lower(cfg, M, N, K, dtype) -> dict:
     info = gt_kernel_info()
     _check(lib().gt_lower(ctypes.byref(to_c(cfg)), M, N, K, dtype_code(dtype), ctypes.byref(info)),
            "gt_lower")
-    return {name: getattr(info, name) for name, _ in gt_kernel_info._fields_}
+    kernel = ctypes.c_int()
+    _check(lib().gt_lower_kernel(ctypes.byref(to_c(cfg)), M, N, K, dtype_code(dtype),
+                                 ctypes.byref(kernel)), "gt_lower_kernel")
+    return {**{name: getattr(info, name) for name, _ in gt_kernel_info._fields_},
+            "kernel": KERNELS[kernel.value]}
 
 
 # ---------------------------------------------------------------------------

@@ -3,10 +3,10 @@
 dimension (Eq.1–4), either input dtype, the MFMA coordinate on some bf16
 spaces, A row-major or K-major (the perceptron layout of §5), and one
 legitimate configuration (Eq.5). Half the cases draw it uniformly by rank
-(which lands on the generic kernel almost always); the other half take a
+(which lands on the generic path almost always); the other half take a
 short random walk over neighbours (Eq.6) from the hand-made 128×128 or 64×64
 start on a four-level space whose extents allow it, the region where the
-register-staged and direct-load kernels apply.
+fast path's ring kernels apply.
 
 The CPU kernel model and the GPU parity test take the same list, so every
 configuration the GPU runs has first been checked for in-bounds global, LDS

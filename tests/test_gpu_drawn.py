@@ -30,16 +30,15 @@ def gt():
 
 def test_drawn_cases_match_oracle(gt, orc):
     dev = torch.device("cuda:0")
-    paths = {"dl": 0, "fast": 0, "generic": 0}
+    kernels = dict.fromkeys(gt.KERNELS, 0)
     for i, (M, N, K, d, dt, mc, akm, cfg) in enumerate(cases_with_env_seeds(gt)):
         smallint = i % 2 == 0
         dist = "smallint" if smallint else ("normal" if dt == "bf16" else "uniform")
         code = gt.dtype_code(dt) | (gt.A_KMAJOR if akm else 0)
         info = gt.lower(cfg, M, N, K, code)
-        path = "dl" if info["dl"] else ("fast" if info["fast"] else "generic")
-        paths[path] += 1
+        kernels[info["kernel"]] += 1
         print(f"case {i}: {M}x{N}x{K} d={d} {dt} {'K-major' if akm else 'row-major'} {dist} "
-              f"{gt.fmt_cfg(cfg)} {path} grid={info['grid_x']}x{info['grid_y']}", flush=True)
+              f"{gt.fmt_cfg(cfg)} {info['kernel']} grid={info['grid_x']}x{info['grid_y']}", flush=True)
         sys.stdout.flush()
         if akm:
             A, B = make_perceptron_inputs(M, N, K, dt, 100 + i, dist)
@@ -56,4 +55,5 @@ def test_drawn_cases_match_oracle(gt, orc):
         else:
             e = float(np.abs(C - ref).max() / max(np.abs(ref).max(), 1e-300))
             assert e <= (1e-5 * K ** 0.5 if dt == "f32" else 2e-3), (i, cfg, e)
-    assert paths["dl"] >= 5 and paths["fast"] >= 10 and paths["generic"] >= 40, paths
+    assert kernels["even"] >= 3 and kernels["ring"] >= 10 and \
+        min(kernels["generic"], kernels["stream"]) >= 10, kernels

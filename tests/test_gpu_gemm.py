@@ -226,12 +226,13 @@ def test_split_k_smallint_bit_exact(gt, orc):
 
 
 SPLITK_PATHS = [
-    # (dtype, configuration, (fast, dl)) at 64x256x1024, split K
-    ("bf16", ((2, 1, 2, 16), (16, 4, 4, 4), (2, 2, 2, 32), 16), (0, 0)),   # generic
-    ("f32", ((2, 1, 2, 16), (16, 4, 4, 4), (2, 2, 2, 32), 16), (1, 0)),    # register-staged
-    ("f32", ((2, 2, 1, 16), (4, 4, 8, 8), (4, 2, 2, 16), 0), (1, 0)),
-    ("bf16", ((1, 1, 2, 32), (4, 8, 2, 16), (4, 2, 1, 32), 32), (1, 1)),   # direct-load
-    ("bf16", ((1, 1, 2, 32), (8, 4, 4, 8), (4, 1, 2, 32), 32), (0, 0)),
+    # (dtype, configuration, kernel) at 64x256x1024, split K
+    ("bf16", ((2, 1, 2, 16), (16, 4, 4, 4), (2, 2, 2, 32), 16), "generic"),
+    ("f32", ((2, 1, 2, 16), (16, 4, 4, 4), (2, 2, 2, 32), 16), "ring"),
+    ("f32", ((2, 2, 1, 16), (4, 4, 8, 8), (4, 2, 2, 16), 0), "ring"),
+    ("bf16", ((2, 1, 1, 32), (2, 4, 8, 16), (8, 1, 1, 32), 32), "ring"),
+    ("bf16", ((1, 1, 2, 32), (4, 8, 2, 16), (4, 2, 1, 32), 32), "even"),
+    ("bf16", ((1, 1, 2, 32), (8, 4, 4, 8), (4, 1, 2, 32), 32), "stream"),
 ]
 
 
@@ -239,11 +240,11 @@ SPLITK_PATHS = [
 def test_split_k_every_path_bit_exact(gt, orc, case):
     """Split K on each kernel path (the clear of C, then fp32 atomics from
     every slice), exact on small integers in any order of the adds."""
-    dt, cfg, path = case
+    dt, cfg, kernel = case
     M, N, K = 64, 256, 1024
     info = gt.lower(cfg, M, N, K, dt)
     note(f"split-K {dt} {cfg} {info}")
-    assert (info["fast"], info["dl"]) == path and info["grid_y"] > 1
+    assert info["kernel"] == kernel and info["grid_y"] > 1
     A, B = make_inputs(M, N, K, dt, 9, "smallint")
     ref = orc.gemm(raw_bytes(A), raw_bytes(B), M, N, K, dt)
     C = run(gt, cfg, A, B)
@@ -344,17 +345,17 @@ def test_search_rejects_a_bad_reference_buffer(gt):
 def test_operands_beyond_4_gib(gt, orc):
     """Operands of several GiB, split 256 ways along K (M = N = 256, bf16).
     At K = 9·2^20 (A and B 4.5 GiB each) byte offsets from each operand's
-    start pass 2^32, which the register-staged and generic kernels address
-    with 64-bit offsets; the direct-load ring, whose per-lane offsets from a
+    start pass 2^32, which the general ring and the generic kernel address
+    with 64-bit offsets; the evenly shared ring, whose per-lane offsets from a
     stage origin are 32-bit, is not chosen there. At K = 7·2^20 the ring is
     chosen and its lane offsets reach 3.74 GB, near their 2^32 limit. Inputs
     in {-1, 0, 1}, so every partial sum, in any order, is an integer of at
     most K < 2^24 in magnitude and exact in fp32: sampled entries, the last
     rows and columns among them, equal the oracle exactly."""
     M = N = 256
-    cases = [(9 << 20, [((1, 2, 4, 32), None, (1, 4, 2, 32), 16, 1, 32, (1, 0)),     # register-staged
-                        ((1, 2, 4, 32), None, (1, 4, 2, 32), 16, 8, 4, (0, 0))]),    # generic
-             (7 << 20, [((1, 2, 4, 32), None, (1, 4, 2, 32), 16, 1, 32, (1, 1))])]   # direct-load
+    cases = [(9 << 20, [((1, 2, 4, 32), None, (1, 4, 2, 32), 16, 1, 32, "ring"),
+                        ((1, 2, 4, 32), None, (1, 4, 2, 32), 16, 8, 4, "generic")]),
+             (7 << 20, [((1, 2, 4, 32), None, (1, 4, 2, 32), 16, 1, 32, "even")])]
     dev = torch.device("cuda:0")
     rng = np.random.default_rng(4)
     rows = np.concatenate([[0, M - 1, M - 1, 0], rng.integers(0, M, 60)])
@@ -365,11 +366,11 @@ def test_operands_beyond_4_gib(gt, orc):
         Ad, Bd = A.to(dev), B.to(dev)
         ref = orc.gemm_entries(raw_bytes(A), raw_bytes(B), M, N, K, "bf16", rows, cols)
         del A, B
-        for m, _, n, mfma, ksub, kblk, path in cfgs:
+        for m, _, n, mfma, ksub, kblk, kernel in cfgs:
             cfg = (m, (K // (ksub * kblk) // 256, 256, ksub, kblk), n, mfma)
             info = gt.lower(cfg, M, N, K, "bf16")
-            note(f"  {gt.fmt_cfg(cfg)} fast={info['fast']} dl={info['dl']} split={info['grid_y']}")
-            assert (info["fast"], info["dl"]) == path and info["grid_y"] == 256
+            note(f"  {gt.fmt_cfg(cfg)} {info['kernel']} split={info['grid_y']}")
+            assert info["kernel"] == kernel and info["grid_y"] == 256
             C = torch.full((M, N), float("nan"), device=dev)
             gt.gemm_run(cfg, Ad, Bd, C)
             torch.cuda.synchronize()

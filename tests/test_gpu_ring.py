@@ -58,7 +58,8 @@ BF16 = [
     ((2, 1, 1, 32), (2, 1, 8, 16), (5, 1, 2, 32), 16),
     ((2, 1, 1, 32), (2, 1, 4, 32), (5, 1, 2, 16), 32),
     ((2, 2, 2, 32), (2, 2, 1, 32), (9, 1, 2, 32), 32),       # 6 loads a wavefront
-    ((2, 2, 4, 32), (2, 4, 2, 32), (4, 1, 2, 32), 16),       # 8 of them spread over 8 wavefronts
+    ((2, 1, 4, 32), (2, 2, 1, 32), (4, 1, 2, 32), 16),       # 8 of A and 4 of B
+    ((2, 2, 1, 32), (2, 1, 8, 32), (5, 1, 2, 16), 32),   # 2 of A and 8 of B
     ((1, 4, 2, 32), (1, 2, 4, 32), (3, 1, 4, 32), 16),       # one stage fills LDS
     ((2, 1, 1, 32), (1, 1, 16, 32), (3, 1, 1, 16), 32),      # a panel of 512 columns
     ((2, 1, 1, 16), (1, 1, 64, 16), (3, 1, 1, 32), 16),      # … of 1024
@@ -69,7 +70,7 @@ BF16 = [
 WIDE = [((1, 1, tm, 16), (2, 1, tn, 16), (k, 1, 1, d))
         for tm, tn in ((1, 16), (16, 1), (1, 32), (32, 1), (2, 16), (16, 2), (4, 8), (8, 4), (1, 64), (64, 1),
                        (2, 32), (32, 2), (4, 16), (16, 4)) for k, d in ((1, 64), (2, 32), (3, 64), (7, 32))] + \
-       [((1, 4, 4, 16), (2, 2, 8, 16), (5, 1, 1, 64)), ((2, 2, 16, 16), (1, 4, 1, 16), (5, 1, 1, 32)),
+       [((1, 2, 4, 16), (2, 2, 8, 16), (5, 1, 1, 64)), ((2, 2, 16, 16), (1, 4, 1, 16), (5, 1, 1, 32)),
         ((1, 1, 2, 16), (1, 2, 32, 16), (9, 1, 1, 32)), ((2, 1, 32, 16), (1, 1, 1, 16), (3, 2, 1, 32))]
 CASES += [(m, n, (*k[:3], max(k[3] >> s, 16)), 0) for m, n, k in WIDE for s in (0, 1)
           if (np.prod(m[1:]) + np.prod(n[1:])) * (k[3] >> s) * 4 <= 163840]
@@ -83,7 +84,7 @@ def test_ring_bit_exact(gt, orc, dtype, case, kmajor):
     m, n, k, mf = case
     M, N, K = (int(np.prod(x)) for x in (m, n, k))
     info = gt.lower((m, k, n, mf), M, N, K, gt.dtype_code(dtype) | (gt.A_KMAJOR if kmajor else 0))
-    assert info["fast"] == 1 and info["ring"] >= 1, info
+    assert info["kernel"] == "ring" and info["ring"] >= 1, info
     A, B = make_inputs(M, N, K, dtype, 23, "smallint")
     ref = orc.gemm(raw_bytes(A), raw_bytes(B), M, N, K, dtype)
     Ad = (A.t().contiguous() if kmajor else A).cuda()
@@ -101,7 +102,7 @@ def test_offsets_past_32_bits(gt):
     A = torch.randint(-1, 2, (M, K), generator=g, device="cuda", dtype=torch.int8).float()
     B = torch.randint(-1, 2, (K, N), generator=g, device="cuda", dtype=torch.int8).float()
     cfg = ((1, 4, 2, 32), (K // 32 // 256, 256, 1, 32), (1, 1, 1, 32), 0)
-    assert gt.lower(cfg, M, N, K, "f32")["fast"] == 1
+    assert gt.lower(cfg, M, N, K, "f32")["kernel"] == "ring"
     C, R = torch.full((M, N), float("nan"), device="cuda"), torch.empty(M, N, device="cuda")
     gt.gemm_run(cfg, A, B, C)
     gt.gt_reference_gemm(A, B, R)
@@ -127,7 +128,7 @@ def test_rows_of_one_load_past_32_bits(gt):
     A, B = _small_integers((M, K), 5), _small_integers((K, N), 6)
     cfg = ((1, 1, 1, 32), (K // 8 // 256, 256, 1, 8), (1, 1, 1, 32), 0)
     info = gt.lower(cfg, M, N, K, "f32")
-    assert info["fast"] == 1 and info["ring"] >= 2
+    assert info["kernel"] == "ring" and info["ring"] >= 2
     C = torch.full((M, N), float("nan"), device="cuda")
     gt.gemm_run(cfg, A, B, C)
     R = torch.zeros(M, N, device="cuda", dtype=torch.float64)
@@ -142,7 +143,7 @@ def test_rows_of_one_panel_load_past_32_bits(gt):
     A, B = _small_integers((M, K), 7), _small_integers((K, N), 8)
     cfg = ((1, 1, 1, 16), (2, 1, 1, 16), (N // 16, 1, 1, 16), 0)
     info = gt.lower(cfg, M, N, K, "f32")
-    assert info["fast"] == 1 and info["ring"] == 2
+    assert info["kernel"] == "ring" and info["ring"] == 2
     C, R = torch.full((M, N), float("nan"), device="cuda"), torch.empty(M, N, device="cuda")
     gt.gemm_run(cfg, A, B, C)
     gt.gt_reference_gemm(A, B, R)

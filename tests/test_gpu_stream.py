@@ -1,13 +1,12 @@
-"""The generic path whose wavefronts read their own operands, at block sizes
-below and above the MFMA's, K ends inside a step, K splits, several
-wavefronts and both layouts: small integers (exact in any order) against the
-oracle, bit for bit."""
+"""The generic path's two kernels: the one whose wavefronts read their own
+operands, at block sizes below and above the MFMA's, K ends inside a step, K
+splits, several wavefronts and both layouts, and the one with shared stages,
+which takes what the other does not. Small integers (exact in any order)
+against the oracle, bit for bit."""
 import numpy as np
 import pytest
 import torch
 
-from test_kernel_model import levels
-from test_stream_model import serves
 from workloads import make_inputs, raw_bytes
 
 pytestmark = pytest.mark.gpu
@@ -51,18 +50,33 @@ F32 = [
     (((3, 1, 1, 8), (5, 1, 4, 16), (3, 1, 1, 1), 0), "k"),       # K = 3
     (((3, 2, 1, 8), (5, 1, 1, 16), (3, 4, 1, 16), 0), "rk"),      # split K
 ]
-CASES = [("bf16", c, lay == "k") for c, w in BF16 for lay in w] + \
-        [("f32", c, lay == "k") for c, w in F32 for lay in w]
+# shared stages: more than 8 wavefronts, rows or blocks no 16-byte load fits,
+# stages shorter than a step, one stage and several, K splits
+GENERIC = [
+    ("bf16", ((3, 4, 1, 16), (5, 4, 1, 16), (7, 1, 2, 16), 16), "rk"),
+    ("bf16", ((3, 1, 1, 16), (5, 1, 1, 2), (7, 1, 1, 16), 16), "r"),
+    ("bf16", ((3, 1, 1, 2), (5, 1, 1, 16), (7, 1, 1, 8), 16), "k"),
+    ("bf16", ((3, 1, 1, 8), (5, 2, 1, 16), (3, 1, 1, 1), 16), "k"),
+    ("bf16", ((3, 1, 4, 32), (3, 1, 4, 32), (1, 1, 1, 8), 16), "rk"),
+    ("bf16", ((3, 1, 4, 32), (3, 1, 4, 32), (3, 2, 1, 8), 16), "rk"),
+    ("f32", ((3, 4, 1, 16), (5, 4, 1, 8), (7, 1, 2, 4), 0), "rk"),
+    ("f32", ((3, 1, 1, 8), (5, 1, 1, 8), (3, 1, 1, 1), 0), "r"),
+    ("f32", ((3, 2, 1, 8), (5, 2, 1, 8), (3, 4, 1, 2), 0), "rk"),
+    ("f32", ((2, 1, 16, 8), (2, 1, 2, 8), (3, 1, 2, 4), 0), "r"),
+]
+CASES = [("stream", "bf16", c, lay == "k") for c, w in BF16 for lay in w] + \
+        [("stream", "f32", c, lay == "k") for c, w in F32 for lay in w] + \
+        [("generic", d, c, lay == "k") for d, c, w in GENERIC for lay in w]
 
 
-@pytest.mark.parametrize("dtype,cfg,kmajor", CASES,
-                         ids=[f"{d}-{'k' if k else 'r'}-{i}" for i, (d, _, k) in enumerate(CASES)])
-def test_stream_bit_exact(gt, orc, dtype, cfg, kmajor):
+@pytest.mark.parametrize("kernel,dtype,cfg,kmajor", CASES,
+                         ids=[f"{g}-{d}-{'k' if k else 'r'}-{i}" for i, (g, d, _, k) in enumerate(CASES)])
+def test_generic_path_bit_exact(gt, orc, kernel, dtype, cfg, kmajor):
     m, n, k, mf = cfg
     cfg = (m, k, n, mf)
     M, N, K = (int(np.prod(x)) for x in (m, n, k))
     info = gt.lower(cfg, M, N, K, gt.dtype_code(dtype) | (gt.A_KMAJOR if kmajor else 0))
-    assert serves(levels(cfg), info, M, N, K, dtype == "bf16", kmajor), (cfg, info)
+    assert info["kernel"] == kernel, (cfg, info)
     A, B = make_inputs(M, N, K, dtype, 29, "smallint")
     ref = orc.gemm(raw_bytes(A), raw_bytes(B), M, N, K, dtype)
     Ad = (A.t().contiguous() if kmajor else A).cuda()

@@ -1,6 +1,6 @@
 """gemm_run called from several host threads at once, each on its own stream
-(default priority), over every kernel path (direct-load ring, register-staged,
-generic, split-K with its clear and atomics): each thread's outputs equal the
+(default priority), over every kernel (evenly shared and general ring, the two
+generic ones, split-K with its clear and atomics): each thread's outputs equal the
 single-threaded outputs bit for bit on small-integer inputs, where every
 partial sum is exact in fp32 whatever the order of the adds."""
 import sys
@@ -16,13 +16,13 @@ pytestmark = pytest.mark.gpu
 
 M, N, K = 64, 256, 1024
 CASES = [
-    # (dtype, configuration) at 64x256x1024
-    ("bf16", ((1, 1, 2, 32), (4, 8, 2, 16), (4, 2, 1, 32), 32)),   # direct-load, split K
-    ("bf16", ((1, 2, 2, 16), (8, 1, 4, 32), (4, 2, 2, 16), 16)),   # direct-load
-    ("f32", ((2, 2, 1, 16), (4, 4, 8, 8), (4, 2, 2, 16), 0)),      # register-staged, split K
-    ("f32", ((2, 2, 1, 16), (16, 1, 8, 8), (4, 2, 2, 16), 0)),     # register-staged
-    ("bf16", ((2, 1, 2, 16), (16, 4, 4, 4), (2, 2, 2, 32), 16)),   # generic, split K
-    ("f32", ((64, 1, 1, 1), (64, 1, 4, 4), (4, 2, 2, 16), 0)),     # generic
+    # (kernel, dtype, configuration) at 64x256x1024
+    ("even", "bf16", ((1, 1, 2, 32), (4, 8, 2, 16), (4, 2, 1, 32), 32)),      # split K
+    ("even", "bf16", ((1, 2, 2, 16), (8, 1, 4, 32), (4, 2, 2, 16), 16)),
+    ("ring", "f32", ((2, 2, 1, 16), (4, 4, 8, 8), (4, 2, 2, 16), 0)),         # split K
+    ("ring", "f32", ((2, 2, 1, 16), (16, 1, 8, 8), (4, 2, 2, 16), 0)),
+    ("generic", "bf16", ((2, 1, 2, 16), (16, 4, 4, 4), (2, 2, 2, 32), 16)),   # split K
+    ("stream", "f32", ((64, 1, 1, 1), (64, 1, 4, 4), (4, 2, 2, 16), 0)),
 ]
 
 
@@ -41,10 +41,10 @@ def test_concurrent_gemm_run_matches_serial(gt, orc):
     for dt in ("bf16", "f32"):
         A, B = make_inputs(M, N, K, dt, 21, "smallint")
         ops[dt] = (A.to(dev), B.to(dev), orc.gemm(raw_bytes(A), raw_bytes(B), M, N, K, dt))
-    for dt, cfg in CASES:
+    for kernel, dt, cfg in CASES:
         info = gt.lower(cfg, M, N, K, dt)
-        print(f"{dt} {gt.fmt_cfg(cfg)} fast={info['fast']} dl={info['dl']} "
-              f"split={info['grid_y']}", flush=True)
+        print(f"{dt} {gt.fmt_cfg(cfg)} {info['kernel']} split={info['grid_y']}", flush=True)
+        assert info["kernel"] == kernel
         Ad, Bd, ref = ops[dt]
         C = torch.full((M, N), float("nan"), device=dev)
         gt.gemm_run(cfg, Ad, Bd, C)
@@ -62,7 +62,7 @@ def test_concurrent_gemm_run_matches_serial(gt, orc):
             for r in range(rounds):
                 n = (t + r) % len(CASES)           # each thread and round its own order
                 for k in list(range(n, len(CASES))) + list(range(n)):
-                    dt, cfg = CASES[k]
+                    _, dt, cfg = CASES[k]
                     Ad, Bd, _ = ops[dt]
                     gt.gemm_run(cfg, Ad, Bd, outs[t][k], stream=s)
             s.synchronize()
@@ -77,7 +77,7 @@ def test_concurrent_gemm_run_matches_serial(gt, orc):
     torch.cuda.synchronize()
     assert not errors, errors
     for t in range(n_threads):
-        for k, (dt, cfg) in enumerate(CASES):
+        for k, (_, dt, cfg) in enumerate(CASES):
             got = outs[t][k].cpu().numpy().astype(np.float64)
             assert np.array_equal(got, ops[dt][2]), (t, cfg)
 

@@ -1,5 +1,7 @@
-"""A CPU model of the fast-path and direct-load GEMM kernels' addressing and
-of the direct-load ring schedule, run over seeded samples of the configurations
+"""A CPU model of the addressing of the evenly shared direct-load kernel and
+of its ring's schedule, and of the generic kernel (the models of the general
+ring and of the wavefronts that read their own operands stand beside their own
+tests, and every launch here is checked by its own kernel's), run over seeded samples of the configurations
 of the 1024³ and 4096³ bf16 spaces and of the 2048³ fp32 space (A row-major
 and K-major) that meet the fast path's shape conditions (plus the known
 fastest 4096³ configurations). The same model run over all
@@ -12,7 +14,7 @@ lane, that
 * every global load of A and B stays inside its operand, for the first and
   last workgroup, split-K slice and stage (the addresses are affine in
   those indices, so the extremes bound all of them);
-* every LDS write (register-staged stores and direct loads) and every LDS
+* every LDS write and every LDS
   fragment read stays inside its stage and the launch's LDS allocation;
 * every C element written belongs to the workgroup's tile;
 * in the direct-load ring, each (stage, load) pair is issued exactly once,
@@ -83,21 +85,6 @@ def a_read_slot(I, BM, CPR, row, grp, cs):
     return (xa ^ (c & 7)) + (c & ~7)
 
 
-def fast_slot(idx, rows, I, CPR):
-    """LDS slot of chunk idx = row·CPR + chunk of a register-staged tile (A
-    [m][k] or B stored [n][k]): the stage-wide layout, swizzled."""
-    return swz(idx)
-
-
-def fast_read_slot(row, grp, c, CPR):
-    """LDS slot a lane of the register-staged path reads for row `row`, chunk
-    c + grp (c = chunk-step·G), as the kernel computes it: a per-row base for
-    the 128-byte line of the chunk-step, then the chunk-step's XOR and line."""
-    j = (c >> 3) if CPR >= 8 else 0
-    x = swz((row << lg(CPR)) + grp + 8 * j) - 8 * j
-    return (x ^ (c & 7)) + (c & ~7)
-
-
 def lg(v):
     r = v.bit_length() - 1
     assert 1 << r == v
@@ -131,38 +118,9 @@ def tiles(L):
     return [(0, 0, 0, 0), (L["gridM"] - 1, L["gridN"] - 1, L["kSplit"] - 1, L["kLoop"] - 1)]
 
 
-def frag_steps(L, CPR, lane):
-    """(wavefront, its M and N coordinates, chunk-step parameters) of the
-    fragment reads."""
-    I = L["I"]
-    G = 64 // I
-    LGCPR = lg(CPR)
-    grp = lane // I
-    for w in range(L["W"]):
-        wm, wn = w % L["wavesM"], w // L["wavesM"]
-        for cs in range(CPR // G):
-            c = cs * G
-            j = (c >> 3) if CPR >= 8 else 0
-            yield w, wm, wn, c, j, LGCPR, grp
-
-
-def check_c_and_frags(L, CPR, achunks, lane, bt_rows=None, a_slots=True):
-    """Fragment reads of the register-staged path (A, and B stored [n][k]
-    like A): each lane's slot is in the tile and is the slot its chunk
-    (row, chunk-step·G + lane group) was written to."""
-    I = L["I"]
-    for w, wm, wn, c, j, LGCPR, grp in frag_steps(L, CPR, lane):
-        for t in range(L["TM"] if a_slots else 0):
-            row = wm * L["WM"] + t * I + lane % I
-            idx = fast_read_slot(row, grp, c, CPR)
-            assert idx.min() >= 0 and idx.max() < achunks
-            assert np.array_equal(idx, fast_slot((row << LGCPR) + c + grp, L["BM"], I, CPR))
-        if bt_rows is not None:
-            for t in range(L["TN"]):
-                row = wn * L["WN"] + t * I + lane % I
-                idx = fast_read_slot(row, grp, c, CPR)
-                assert idx.min() >= 0 and idx.max() < bt_rows << LGCPR
-                assert np.array_equal(idx, fast_slot((row << LGCPR) + c + grp, bt_rows, I, CPR))
+def check_c(L):
+    """The fast path's stores of C stay inside the workgroup's tile."""
+    I, lane = L["I"], np.arange(64)
     for w in range(L["W"]):
         wm, wn = w % L["wavesM"], w // L["wavesM"]
         for e in range(I * I // 64):
@@ -173,70 +131,21 @@ def check_c_and_frags(L, CPR, achunks, lane, bt_rows=None, a_slots=True):
         assert cols.max() < L["BN"]
 
 
-def check_fast(L, info, M, N, K, vec=8, akm=False):
-    VEC, LGV = vec, lg(vec)
-    I = L["I"]
-    CPR = L["BK"] // VEC
-    LGCPR = lg(CPR)
-    nthr = 64 * L["W"]
-    BM, BN = L["BM"], L["BN"]
-    achunks = BM << LGCPR
-    lgnbn = lg(BN) - LGV
-    bblocks = CPR << lgnbn
-    stage = achunks + (BN << LGCPR)
-    assert (2 if info["dbuf"] else 1) * stage * 16 <= info["lds_bytes"] <= LDS_MAX
-    tid = np.arange(nthr)
-    prefetch = max(-(-achunks // (nthr * 8)), -(-bblocks // nthr)) == 1
-    for gm, gn, z, l in tiles(L):
-        kbase = (l * L["kSplit"] + z) * L["BK"]
-        a0, b0 = gm * BM * K + kbase, gn * BN + kbase * N
-        if akm:
-            # A K-major: VEC×VEC blocks of W (K×M), like B's
-            lgnbm = lg(BM) - LGV
-            ablocks = CPR << lgnbm
-            if prefetch:
-                nab = min(8 // VEC, -(-ablocks // nthr))
-                ab = np.concatenate([np.minimum(tid + i * nthr, ablocks - 1) for i in range(nab)])
-            else:
-                ab = np.arange(ablocks)
-            nm, kb = ab & ((1 << lgnbm) - 1), ab >> lgnbm
-            for j in range(VEC):
-                addr = gm * BM + (kbase + (kb << LGV) + j) * M + (nm << LGV)
-                assert addr.min() >= 0 and addr.max() + VEC <= K * M
-                assert fast_slot((((nm << LGV) + j) << LGCPR) + kb, BM, I, CPR).max() < achunks
-            # every A chunk of the stage is written, each to its own slot
-            dst = np.concatenate([fast_slot((((nm << LGV) + j) << LGCPR) + kb, BM, I, CPR)
-                                  for j in range(VEC)])
-            assert len(np.unique(dst)) == achunks
-        elif prefetch:
-            ta = np.minimum(tid, achunks - 1)
-            na = min(8, -(-achunks // nthr))
-            dst = []
-            for i in range(na):
-                e = ta + i * nthr
-                addr = a0 + (ta >> LGCPR) * K + ((ta & (CPR - 1)) << LGV) + i * (nthr >> LGCPR) * K
-                assert addr.min() >= 0 and addr.max() + VEC <= M * K
-                # the chunk at addr is row e / CPR, chunk e mod CPR of the tile
-                assert np.array_equal(addr, a0 + (e >> LGCPR) * K + ((e & (CPR - 1)) << LGV))
-                dst.append(fast_slot(e, BM, I, CPR))
-            dst = np.concatenate(dst)
-            assert dst.max() < achunks and len(np.unique(dst)) == achunks
-        else:
-            e = np.arange(achunks)
-            addr = a0 + (e >> LGCPR) * K + ((e & (CPR - 1)) << LGV)
-            dst = fast_slot(e, BM, I, CPR)
-            assert addr.max() + VEC <= M * K and dst.max() < achunks
-            assert len(np.unique(dst)) == achunks
-        b = np.minimum(tid, bblocks - 1) if prefetch else np.arange(bblocks)
-        nb, kb = b & ((1 << lgnbn) - 1), b >> lgnbn
-        bdst = []
-        for j in range(VEC):
-            addr = b0 + ((kb << LGV) + j) * N + (nb << LGV)
-            assert addr.min() >= 0 and addr.max() + VEC <= K * N
-            bdst.append(fast_slot((((nb << LGV) + j) << LGCPR) + kb, BN, I, CPR))
-        bdst = np.concatenate(bdst)
-        assert bdst.max() < BN << LGCPR and len(np.unique(bdst)) == BN << LGCPR
-    check_c_and_frags(L, CPR, achunks, np.arange(64), bt_rows=BN)
+def check_launch(L, info, M, N, K, dtype, akm):
+    """The model of the kernel that the lowering chose."""
+    from test_ring_model import check_ring
+    from test_stream_model import check_stream
+    if info["kernel"] == "even":
+        assert not akm and info["dl"]
+        check_dl(L, info, M, N, K)
+    elif info["kernel"] == "ring":
+        check_ring(L, info, M, N, K, dtype == "bf16", akm)
+        check_c(L)
+    elif info["kernel"] == "stream":
+        check_stream(L, info, M, N, K, dtype == "bf16", akm)
+        check_generic(L, info, M, N, K, dtype, akm)   # (the launch, the tile map and C)
+    else:
+        check_generic(L, info, M, N, K, dtype, akm)
 
 
 def check_dl(L, info, M, N, K):
@@ -311,7 +220,7 @@ def check_dl(L, info, M, N, K):
                 slot = a_read_slot(I, BM, CPR, row, lane // I, cs)
                 assert slot.min() >= 0 and slot.max() < achunks
                 assert np.array_equal(held[slot], row * CPR + cs * G + lane // I)
-    check_c_and_frags(L, CPR, achunks, lane, a_slots=False)
+    check_c(L)
     ring_schedule(TM * TN, NCS, cap, ninst, ns, L["kLoop"])
 
 
@@ -421,7 +330,7 @@ def _fast_for(T, I, mf, vec, esz):
 
 
 def _run(gt, cfgs, D, dtype="bf16", akm=False):
-    n = {"dl": 0, "fast": 0}
+    n = dict.fromkeys(gt.KERNELS, 0)
     code = gt.dtype_code(dtype) | (gt.A_KMAJOR if akm else 0)
     for c in cfgs:
         try:
@@ -430,19 +339,14 @@ def _run(gt, cfgs, D, dtype="bf16", akm=False):
             continue  # (TM, TN) without an instantiation
         L = levels(c)
         assert (info["BM"], info["BN"], info["BK"], info["waves"]) == (L["BM"], L["BN"], L["BK"], L["W"])
-        if info["dl"]:
-            assert not akm
-            check_dl(L, info, D, D, D)
-            n["dl"] += 1
-        elif info["fast"]:
-            check_fast(L, info, D, D, D, vec=8 if dtype == "bf16" else 4, akm=akm)
-            n["fast"] += 1
+        check_launch(L, info, D, D, D, dtype, akm)
+        n[info["kernel"]] += 1
     return n
 
 
 def test_model_sample_1024(gt):
     n = _run(gt, random.Random(4).sample(fast_candidates(1024), 3000), 1024)
-    assert n["dl"] > 100 and n["fast"] > 100, n
+    assert n["even"] > 100 and n["ring"] > 100, n
 
 
 def test_model_sample_4096(gt):
@@ -453,15 +357,15 @@ def test_model_sample_4096(gt):
              ((16, 4, 2, 32), (64, 1, 4, 16), (16, 2, 4, 32), 32)]
     sample = known + random.Random(5).sample(cands, 3000)
     n = _run(gt, sample, 4096)
-    assert n["dl"] > 100 and n["fast"] > 100, n
+    assert n["even"] > 100 and n["ring"] > 100, n
 
 
 @pytest.mark.parametrize("akm", [False, True])
 def test_model_sample_f32(gt, akm):
-    """fp32 register-staged path, A row-major and K-major (2048³)."""
+    """The fp32 ring, A row-major and K-major (2048³)."""
     cands = fast_candidates(2048, "f32")
     n = _run(gt, random.Random(6).sample(cands, min(2000, len(cands))), 2048, "f32", akm)
-    assert n["fast"] > 500 and n["dl"] == 0, n
+    assert n["ring"] > 500 and n["even"] == 0, n
 
 
 @pytest.mark.parametrize("ns", range(2, 9))
@@ -678,7 +582,7 @@ def check_fill(n):
 
 
 def run_models(gt, cfgs, M, N, K, dtype="bf16", akm=False):
-    n = {"dl": 0, "fast": 0, "generic": 0}
+    n = dict.fromkeys(gt.KERNELS, 0)
     code = gt.dtype_code(dtype) | (gt.A_KMAJOR if akm else 0)
     for c in cfgs:
         info = gt.lower(c, M, N, K, code)
@@ -687,15 +591,8 @@ def run_models(gt, cfgs, M, N, K, dtype="bf16", akm=False):
         # MFMA size, MFMA tiles per wavefront)
         assert (info["BM"], info["BN"], info["BK"], info["waves"], info["I"], info["TM"],
                 info["TN"]) == (L["BM"], L["BN"], L["BK"], L["W"], L["I"], L["TM"], L["TN"]), c
-        if info["dl"]:
-            check_dl(L, info, M, N, K)
-            n["dl"] += 1
-        elif info["fast"]:
-            check_fast(L, info, M, N, K, vec=8 if dtype == "bf16" else 4, akm=akm)
-            n["fast"] += 1
-        else:
-            check_generic(L, info, M, N, K, dtype, akm)
-            n["generic"] += 1
+        check_launch(L, info, M, N, K, dtype, akm)
+        n[info["kernel"]] += 1
         if L["kSplit"] > 1:
             check_fill(M * N)
     return n
@@ -728,7 +625,7 @@ def test_random_search_candidates_4096(gt, orc, seed):
     gt.tune_random(sp, budget=1000, seed=seed, cost_fn=lambda c, r: (timed.append(c), 1.0)[1])
     assert len(timed) == 1000
     n = run_models(gt, timed, D, D, D)
-    assert n["generic"] > 900, n
+    assert n["generic"] + n["stream"] > 900 and min(n["generic"], n["stream"]) > 100, n
     osp = orc.Space(D, D, D, (4, 4, 4), "bf16", True)
     oversized = 0
     for r in _draws(sp.size(), seed, 3000):
@@ -754,7 +651,7 @@ def test_model_legitimate_sample(gt, space):
         if sp.legit(c):
             cfgs.append(c)
     n = run_models(gt, cfgs, M, N, K, dt)
-    assert n["generic"] > 200, n
+    assert n["generic"] + n["stream"] > 200, n
 
 
 def test_model_drawn_cases(gt):
@@ -762,11 +659,11 @@ def test_model_drawn_cases(gt):
     shapes, one to four levels, both dtypes and layouts, every path) passes
     the kernel models before any of it reaches a GPU."""
     from drawn_cases import cases_with_env_seeds
-    n = {"dl": 0, "fast": 0, "generic": 0}
+    n = dict.fromkeys(gt.KERNELS, 0)
     for M, N, K, d, dt, mc, akm, cfg in cases_with_env_seeds(gt):
         for k, v in run_models(gt, [cfg], M, N, K, dt, akm).items():
             n[k] += v
-    assert n["dl"] >= 5 and n["fast"] >= 10 and n["generic"] >= 40, n
+    assert n["even"] >= 3 and n["ring"] >= 10 and n["generic"] >= 10 and n["stream"] >= 10, n
 
 
 def _wide(K=256, N=256):
@@ -785,14 +682,14 @@ def test_direct_load_offsets_stay_32_bit(gt, case):
     """The direct-load kernel keeps each lane's global offset from the stage
     origin in 32 bits (bytes below 2^32 while BM·K and BK·N stay below 2^31
     elements). Shapes that large are legitimate (operands of several GiB fit
-    in HBM), so lowering leaves the ring for the register-staged kernel,
-    whose offsets are 64-bit, from that bound on (one row early: at the bound
+    in HBM), so lowering leaves it for the general ring, whose loads step
+    64-bit addresses there, from that bound on (one row early: at the bound
     itself the offsets would still fit); beyond it they would wrap."""
     M, N, K, cfg, dl, wraps = case
     sp = gt.Space(M, N, K, (4, 4, 4), "bf16", True)
     assert sp.legit(cfg)
     info = gt.lower(cfg, M, N, K, "bf16")
-    assert info["fast"] == 1 and info["dl"] == dl, info
+    assert info["kernel"] == ("even" if dl else "ring") and info["dl"] == dl, info
     # the ring's per-lane offsets from the stage origins, over every A and B
     # slot of a stage (the formulas of the direct-load model above)
     L = levels(cfg)
@@ -812,7 +709,7 @@ def test_model_every_configuration_of_the_search_spaces(gt):
     search test tunes over (a search may time any of them, whatever the
     timings), every path, passes the kernel models."""
     from drawn_cases import draw_small_spaces
-    n = {"dl": 0, "fast": 0, "generic": 0}
+    n = dict.fromkeys(gt.KERNELS, 0)
     total = 0
     for M, N, K, d, dt, mc, akm in draw_small_spaces(gt):
         sp = gt.Space(M, N, K, d, dt, mc, a_kmajor=akm)
@@ -820,4 +717,4 @@ def test_model_every_configuration_of_the_search_spaces(gt):
         for k, v in run_models(gt, legit, M, N, K, dt, akm).items():
             n[k] += v
         total += len(legit)
-    assert sum(n.values()) == total and n["generic"] > 0 and n["fast"] > 0, n
+    assert sum(n.values()) == total and min(n["generic"], n["stream"], n["ring"]) > 0, n

@@ -69,8 +69,10 @@ def symbol(info, dtype, akm):
     dt = 1 if dtype == "bf16" else 0
     cpr = info["BK"] // (8 if dtype == "bf16" else 4) if info["fast"] else 0
     I, TM, TN = info["I"], info["TM"], info["TN"]
-    if info["dl"]:
+    if info["kernel"] == "even":
         return f"_ZN2gt14gemm_kernel_dlILi{I}ELi{TM}ELi{TN}ELi{cpr}EEEvNS_5KArgsE"
+    if info["kernel"] == "stream":
+        return f"_ZN2gt18gemm_kernel_streamILi{dt}ELi{I}ELi{TM}ELi{TN}ELb{int(akm)}EEEvNS_5KArgsE"
     name = "15gemm_kernel_akm" if akm and info["fast"] else "11gemm_kernel"
     return f"_ZN2gt{name}ILi{dt}ELi{I}ELi{TM}ELi{TN}ELi{cpr}EEEvNS_5KArgsE"
 
@@ -105,6 +107,7 @@ def test_every_legitimate_launch_fits_its_compiled_kernel(gt, kernels, space):
     rng = random.Random(M + 3 * N + 7 * K + akm)
     size = sp.size()
     legit = tries = 0
+    seen = set()
     while legit < samples and tries < 200 * samples:
         tries += 1
         c = sp.unrank(rng.randrange(size))
@@ -112,11 +115,13 @@ def test_every_legitimate_launch_fits_its_compiled_kernel(gt, kernels, space):
             continue          # the library does not lower these
         legit += 1
         info = gt.lower(c, M, N, K, code)
+        seen.add(info["kernel"])
         k = kernels.get(symbol(info, dt, akm))
         assert k is not None, (c, info)   # the lowering table and the objects agree
         assert fits(k, info), (c, info, {f: k[f] for f in (".vgpr_count", ".agpr_count",
                                ".max_flat_workgroup_size", ".group_segment_fixed_size")})
     assert legit == samples
+    assert {"generic", "stream"} <= seen, seen
 
 
 def test_the_ring_kernels_keep_their_fragments_in_registers(kernels):

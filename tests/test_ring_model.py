@@ -4,6 +4,7 @@ element of a stage in LDS, what its fragment reads find there, how far its
 global addresses reach, and the order of loads, waits, barriers and reads of
 its ring, over every kernel shape and over the launches the lowering chooses.
 The model restates the kernel's index formulas; it shares no code with it."""
+import functools
 import itertools
 import os
 import random
@@ -119,55 +120,61 @@ SHAPES = [(I, TM, TN, cpr) for I in (16, 32) for cpr in (2, 4, 8, 16) if cpr >= 
           for TM, TN in itertools.product((1, 2, 4, 8, 16), repeat=2) if TM * TN * I * I // 64 <= 256]
 
 
+@functools.lru_cache(maxsize=None)
+def check_reads(bf16, ak, I, TM, TN, cpr, wavesM, wavesN):
+    """Every fragment read of every wavefront finds the element its MFMA lane
+    needs."""
+    vec = 8 if bf16 else 4
+    G = 64 // I
+    grp, l0 = LANE // I, LANE % I
+    i16, g16 = LANE & 15, LANE >> 4
+    BK, WM, WN, BM = cpr * vec, TM * I, TN * I, wavesM * TM * I
+    outer, kk, na = stage(I, TM, TN, cpr, wavesM, wavesN, ak, bf16)
+
+    def panel_read(wi, t, W, cs, q):      # fp32
+        col = t * I + l0
+        if flip_panel(I, W // 4):
+            col = col ^ ((grp & 1) << 4)
+        return wi * BK * W + grp * 4 * W + col + (cs * G * 4 + q) * W
+
+    for wm, wn, cs in itertools.product(range(wavesM), range(wavesN), range(cpr // G)):
+        for t in range(TM):
+            row = wm * WM + t * I + l0
+            for q in range(4 if not bf16 else 8):
+                k = (cs * G + grp) * vec + q
+                if ak:
+                    w = panel_read(wm, t, WM, cs, q)
+                elif planes(bf16, I, cpr):
+                    w = (cs * 4 * BM + swz((row << 2) + grp)) * 8 + q
+                else:
+                    w = (row * cpr + ((fswz(l0, cpr) ^ grp) ^ (cs * G))) * vec + q
+                assert (outer[w] == row).all() and (kk[w] == k).all()
+        for t in range(TN):
+            want = wn * WN + t * I + l0
+            if not bf16:
+                for q in range(4):
+                    w = na + panel_read(wn, t, WN, cs, q)
+                    assert (outer[w] == want).all() and (kk[w] == (cs * G + grp) * 4 + q).all()
+                continue
+            # the transposing read: lane l of a 16-lane group gets, as its
+            # j-th value, element l & 3 of what lane 4j + (l >> 2) addresses
+            C = WN // 8
+            kr = (g16 >> 1 if I == 32 else g16) * 8 + (i16 >> 2)
+            col = t * I + (16 * (g16 & 1) if I == 32 else 0) + 4 * (i16 & 3)
+            x = np.array([bswz(int(v), C) for v in kr])
+            at = na + wn * BK * WN + (kr * C + ((col >> 3) ^ x)) * 8 + (col & 4)
+            for hh, j in itertools.product(range(2), range(4)):
+                w = at[16 * g16 + 4 * j + (i16 >> 2)] + (cs * G * 8 + 4 * hh) * WN + (LANE & 3)
+                assert (outer[w] == want).all()
+                assert (kk[w] == cs * G * 8 + (LANE // I) * 8 + 4 * hh + j).all()
+
+
 @pytest.mark.parametrize("bf16,ak", [(False, False), (False, True), (True, False)])
 def test_reads_find_what_the_loads_wrote(bf16, ak):
-    vec = 8 if bf16 else 4
     for I, TM, TN, cpr in SHAPES:
-        G = 64 // I
-        grp, l0 = LANE // I, LANE % I
-        i16, g16 = LANE & 15, LANE >> 4
         for wavesM, wavesN in ((1, 1), (2, 1), (1, 2), (4, 2)):
-            BK, WM, WN, BM = cpr * vec, TM * I, TN * I, wavesM * TM * I
-            if (BM + wavesN * WN) * cpr * 16 > LDS_MAX:
-                continue
-            outer, kk, na = stage(I, TM, TN, cpr, wavesM, wavesN, ak, bf16)
-
-            def panel_read(wi, t, W, cs, q):      # fp32
-                col = t * I + l0
-                if flip_panel(I, W // 4):
-                    col = col ^ ((grp & 1) << 4)
-                return wi * BK * W + grp * 4 * W + col + (cs * G * 4 + q) * W
-
-            for wm, wn, cs in itertools.product(range(wavesM), range(wavesN), range(cpr // G)):
-                for t in range(TM):
-                    row = wm * WM + t * I + l0
-                    for q in range(4 if not bf16 else 8):
-                        k = (cs * G + grp) * vec + q
-                        if ak:
-                            w = panel_read(wm, t, WM, cs, q)
-                        elif planes(bf16, I, cpr):
-                            w = (cs * 4 * BM + swz((row << 2) + grp)) * 8 + q
-                        else:
-                            w = (row * cpr + ((fswz(l0, cpr) ^ grp) ^ (cs * G))) * vec + q
-                        assert (outer[w] == row).all() and (kk[w] == k).all()
-                for t in range(TN):
-                    want = wn * WN + t * I + l0
-                    if not bf16:
-                        for q in range(4):
-                            w = na + panel_read(wn, t, WN, cs, q)
-                            assert (outer[w] == want).all() and (kk[w] == (cs * G + grp) * 4 + q).all()
-                        continue
-                    # the transposing read: lane l of a 16-lane group gets, as its
-                    # j-th value, element l & 3 of what lane 4j + (l >> 2) addresses
-                    C = WN // 8
-                    kr = (g16 >> 1 if I == 32 else g16) * 8 + (i16 >> 2)
-                    col = t * I + (16 * (g16 & 1) if I == 32 else 0) + 4 * (i16 & 3)
-                    x = np.array([bswz(int(v), C) for v in kr])
-                    at = na + wn * BK * WN + (kr * C + ((col >> 3) ^ x)) * 8 + (col & 4)
-                    for hh, j in itertools.product(range(2), range(4)):
-                        w = at[16 * g16 + 4 * j + (i16 >> 2)] + (cs * G * 8 + 4 * hh) * WN + (LANE & 3)
-                        assert (outer[w] == want).all()
-                        assert (kk[w] == cs * G * 8 + (LANE // I) * 8 + 4 * hh + j).all()
+            if (wavesM * TM + wavesN * TN) * I * cpr * 16 <= LDS_MAX:
+                check_reads(bf16, ak, I, TM, TN, cpr, wavesM, wavesN)
 
 
 def replay(ns, kLoop, NCS, na, nb, most, SG, streams):
@@ -238,6 +245,29 @@ def replay(ns, kLoop, NCS, na, nb, most, SG, streams):
     return ev
 
 
+@functools.lru_cache(maxsize=None)
+def check_order(ns, kLoop, NCS, na, nb, most, SG, streams):
+    cnt = na + nb
+    issued, ready, last_read, bars, landed = [], set(), {}, 0, set()
+    for e in replay(ns, kLoop, NCS, na, nb, most, SG, streams):
+        if e[0] == "load":
+            if e[1] is not None:
+                assert e[1] < kLoop
+                if e[1] >= ns:
+                    assert last_read[e[1] - ns] < bars
+            issued.append(e[1])
+        elif e[0] == "wait":
+            done = issued[:len(issued) - e[1]] if e[1] else issued
+            landed |= {s for s in set(done) if done.count(s) == cnt}
+        elif e[0] == "bar":
+            bars += 1
+            ready |= landed
+        else:
+            assert cnt == 0 or e[1] in ready
+            last_read[e[1]] = bars
+    assert all(issued.count(s) == cnt for s in range(kLoop))
+
+
 @pytest.mark.parametrize("streams", [False, True])
 @pytest.mark.parametrize("ns", range(1, 9))
 def test_ring_order(ns, streams):
@@ -247,25 +277,49 @@ def test_ring_order(ns, streams):
     for SG, kLoop, NCS, most in itertools.product((1, 2, 4), (1, 2, 3, 4, 7, 8, 20), (1, 2, 4, 8),
                                               (1, 2, 3, 4, 5, 8, 9, 16, 33)):
         for na, nb in {(most, most), (most, 0), (0, most), (most - 1, most), (most, most // 2)}:
-            cnt = na + nb
-            issued, ready, last_read, bars, landed = [], set(), {}, 0, set()
-            for e in replay(ns, kLoop, NCS, na, nb, most, SG, streams):
-                if e[0] == "load":
-                    if e[1] is not None:
-                        assert e[1] < kLoop
-                        if e[1] >= ns:
-                            assert last_read[e[1] - ns] < bars
-                    issued.append(e[1])
-                elif e[0] == "wait":
-                    done = issued[:len(issued) - e[1]] if e[1] else issued
-                    landed |= {s for s in set(done) if done.count(s) == cnt}
-                elif e[0] == "bar":
-                    bars += 1
-                    ready |= landed
-                else:
-                    assert cnt == 0 or e[1] in ready
-                    last_read[e[1]] = bars
-            assert all(issued.count(s) == cnt for s in range(kLoop))
+            check_order(ns, kLoop, NCS, na, nb, most, SG, streams)
+
+
+def check_bounds(L, info, M, N, K, bf16, akm):
+    """The ring fits LDS and K, the operands' last tile and stage are reached
+    and not passed, offsets fit 32 bits unless the loads step 64-bit
+    addresses. Returns the loads of a stage."""
+    size, vec = (2, 8) if bf16 else (4, 4)
+    I, TM, TN, cpr, ns = info["I"], info["TM"], info["TN"], info["BK"] // vec, info["ring"]
+    BM, BN, BK = info["BM"], info["BN"], info["BK"]
+    assert 1 <= ns <= (8 if bf16 else 3) and (info["dl"] or ns <= L["kLoop"])
+    assert info["lds_bytes"] == ns * (BM + BN) * BK * size <= LDS_MAX
+    lda = M if akm else K
+    gm, gn, last = L["gridM"] - 1, L["gridN"] - 1, (L["kLoop"] * L["kSplit"] - 1) * BK
+    orgA = last * M + gm * BM if akm else gm * BM * K + last
+    orgB = last * N + gn * BN
+    A, B = loads(I, TM, TN, cpr, L["wavesM"], L["wavesN"], akm, lda, N, bf16)
+    for side, org, end in ((A, orgA, M * K), (B, orgB, K * N)):
+        assert min(off.min() for _, _, off in side) == 0
+        assert org + max(off.max() for _, _, off in side) + vec == end, info
+        wide = max(BK * M if akm else BM * K, BK * N) * size >= 1 << 32
+        assert wide or max(off.max() for _, _, off in side) * size < 1 << 32
+    return A, B
+
+
+def check_ring(L, info, M, N, K, bf16, akm):
+    """One launch of the ring kernel: its addresses, its reads of LDS and the
+    order of each of its wavefronts."""
+    A, B = check_bounds(L, info, M, N, K, bf16, akm)
+    I, TM, TN, cpr = info["I"], info["TM"], info["TN"], info["BK"] // (8 if bf16 else 4)
+    check_reads(bf16, akm, I, TM, TN, cpr, L["wavesM"], L["wavesN"])
+    nw, NCS = L["W"], cpr // (64 // I)
+    acc = TM * TN * I * I // 64
+    spare = 32 if not bf16 and cpr == 16 and acc == 256 else 80
+    streams = I == 16 and acc + 9 * (TM + TN) + spare > (512 if acc + 96 > 256 else 256)
+    SG = min(TM * TN, 4) if bf16 else 4
+    most = max(-(-info[x] * cpr // (64 * nw)) for x in ("BM", "BN"))
+    for w in range(nw):
+        na, nb = (sum(1 for v, _, _ in side if v == w) for side in (A, B))
+        assert max(na, nb) <= most
+        wide = max(info["BK"] * M if akm else info["BM"] * K, info["BK"] * N) * (2 if bf16 else 4) >= 1 << 32
+        # the schedule repeats from one turn of the ring to the next
+        check_order(info["ring"], min(L["kLoop"], 20), NCS, na, nb, 9 if wide else most, SG, streams)
 
 
 @pytest.mark.parametrize("dt,akm", [("f32", False), ("f32", True), ("bf16", False)])
@@ -278,7 +332,6 @@ def test_lowered_launches_stay_in_bounds(gt, space, dt, akm):
     from test_kernel_model import levels
     M, N, K = space
     bf16 = dt == "bf16"
-    size, vec = (2, 8) if bf16 else (4, 4)
     sp = gt.Space(M, N, K, (4, 4, 4), dt, bf16, a_kmajor=akm)
     rng = random.Random(M + N + akm)
     code = gt.dtype_code(dt) | (gt.A_KMAJOR if akm else 0)
@@ -293,20 +346,10 @@ def test_lowered_launches_stay_in_bounds(gt, space, dt, akm):
             continue
         seen += 1
         L = levels(c)
-        I, TM, TN, cpr, ns = info["I"], info["TM"], info["TN"], info["BK"] // vec, info["ring"]
-        BM, BN, BK = info["BM"], info["BN"], info["BK"]
-        assert 1 <= ns <= (8 if bf16 else 3) and (info["dl"] or ns <= L["kLoop"])
-        assert info["lds_bytes"] == ns * (BM + BN) * BK * size <= LDS_MAX
-        lda = M if akm else K
-        gm, gn, last = L["gridM"] - 1, L["gridN"] - 1, (L["kLoop"] * L["kSplit"] - 1) * BK
-        orgA = last * M + gm * BM if akm else gm * BM * K + last
-        orgB = last * N + gn * BN
-        A, B = loads(I, TM, TN, cpr, L["wavesM"], L["wavesN"], akm, lda, N, bf16)
-        for side, org, end in ((A, orgA, M * K), (B, orgB, K * N)):
-            assert min(off.min() for _, _, off in side) == 0
-            assert org + max(off.max() for _, _, off in side) + vec == end, c
-            wide = max(BK * M if akm else BM * K, BK * N) * size >= 1 << 32
-            assert wide or max(off.max() for _, _, off in side) * size < 1 << 32
+        if info["kernel"] == "ring":
+            check_ring(L, info, M, N, K, bf16, akm)
+        else:       # the evenly shared loads reach the same places
+            check_bounds(L, info, M, N, K, bf16, akm)
     assert seen >= 80, (seen, tries)
 
 

@@ -102,6 +102,50 @@ def test_panel_reads(I):
                 check_panel_reads(I, TX, width, blk)
 
 
+def check_stream(L, info, M, N, K, bf16, akm):
+    """One launch: the last whole and partial steps of the first and last
+    workgroup, slice and wavefront stay inside the operands and the LDS."""
+    size = 2 if bf16 else 4
+    I, KL = L["I"], 8 if bf16 else 4
+    KS = KL * (64 // I)
+    run = K if L["kSplit"] == 1 else L["BK"]
+    skip = 0 if L["kSplit"] == 1 else (L["kSplit"] - 1) * L["BK"]
+    runs = 1 if L["kSplit"] == 1 else L["kLoop"]
+    per, left = divmod(run, KS)
+    assert left == 0 or L["kSplit"] == 1
+    for gm, gn, z in ((0, 0, 0), (L["gridM"] - 1, L["gridN"] - 1, L["kSplit"] - 1)):
+        for w in {0, L["W"] - 1}:
+            wm, wn = w % L["wavesM"], w // L["wavesM"]
+            row0, col0 = gm * L["BM"] + wm * L["WM"], gn * L["BN"] + wn * L["WN"]
+            # the last whole step, and the partial one
+            last = z * L["BK"] + (runs - 1) * (run + skip)
+            for k, kv in ([(last + (per - 1) * KS, KS)] if per else []) + ([(last + per * KS, left)] if left else []):
+                for x0, ld, X, TX, width, blk, step_rows in (
+                        (col0, N, N, L["TN"], L["WN"], L["blkN"], True),
+                        (row0, M if akm else K, M, L["TM"], L["WM"], L["blkM"], akm)):
+                    for t in range(TX):
+                        if not step_rows:      # row-major A
+                            rows, kk = in_tile(t, LANE % I, I, blk), LANE // I * KL
+                            off = np.where(kk < kv, rows * K + kk, 0)
+                            at, words = x0 * K + k + off, KL
+                            assert off.max() * size < 1 << 32 and at.max() + words <= M * K
+                        elif bf16:
+                            kr, off, put, _, _ = panel_bf16(I, TX, width, ld, blk)[t]
+                            off = np.where(kr < kv, off, 0)
+                            at = k * ld + x0 + off // 2
+                            assert off.max() < 1 << 32 and at.max() + 8 <= K * X
+                            assert ((at * 2) % 16 == 0).all()
+                            assert put.max() + 16 <= KS * width * 2
+                        else:
+                            kr = LANE // I * 4 + np.arange(4)[:, None]
+                            off = np.where(kr < kv, kr * ld + in_tile(t, LANE % I, I, blk), 0)
+                            at = k * ld + x0 + off
+                            assert off.max() * 4 < 1 << 32 and at.max() < K * X
+                        assert at.min() >= 0
+    if bf16:
+        assert L["W"] * KS * (max(L["WM"], L["WN"]) if akm else L["WN"]) * 2 <= info["lds_bytes"]
+
+
 SPACES = [(1360, 1200, 720, "bf16", False), (1360, 1200, 720, "bf16", True), (1000, 1000, 1000, "bf16", False),
           (1000, 1000, 1000, "f32", False), (1000, 1000, 1000, "f32", True), (2048, 2048, 2048, "bf16", True),
           (96, 80, 48, "bf16", False), (130, 74, 36, "f32", False), (4096, 4096, 4096, "bf16", False)]
@@ -113,7 +157,6 @@ def test_addresses_of_lowered_launches(gt, space):
     bf16 = dt == "bf16"
     sp = gt.Space(M, N, K, (4, 4, 4), dt, bf16, a_kmajor=akm)
     rng = random.Random(M + K + akm)
-    size = 2 if bf16 else 4
     seen = tries = 0
     while seen < 120 and tries < 20000:
         tries += 1
@@ -122,45 +165,9 @@ def test_addresses_of_lowered_launches(gt, space):
             continue
         info = gt.lower(c, M, N, K, gt.dtype_code(dt) | (gt.A_KMAJOR if akm else 0))
         L = levels(c)
-        if not serves(L, info, M, N, K, bf16, akm):
+        assert (info["kernel"] == "stream") == serves(L, info, M, N, K, bf16, akm), (c, info)
+        if info["kernel"] != "stream":
             continue
         seen += 1
-        I, KL = L["I"], 8 if bf16 else 4
-        KS = KL * (64 // I)
-        run = K if L["kSplit"] == 1 else L["BK"]
-        skip = 0 if L["kSplit"] == 1 else (L["kSplit"] - 1) * L["BK"]
-        runs = 1 if L["kSplit"] == 1 else L["kLoop"]
-        per, left = divmod(run, KS)
-        assert left == 0 or L["kSplit"] == 1
-        for gm, gn, z in ((0, 0, 0), (L["gridM"] - 1, L["gridN"] - 1, L["kSplit"] - 1)):
-            for w in {0, L["W"] - 1}:
-                wm, wn = w % L["wavesM"], w // L["wavesM"]
-                row0, col0 = gm * L["BM"] + wm * L["WM"], gn * L["BN"] + wn * L["WN"]
-                # the last whole step, and the partial one
-                last = z * L["BK"] + (runs - 1) * (run + skip)
-                for k, kv in ([(last + (per - 1) * KS, KS)] if per else []) + ([(last + per * KS, left)] if left else []):
-                    for x0, ld, X, TX, width, blk, step_rows in (
-                            (col0, N, N, L["TN"], L["WN"], L["blkN"], True),
-                            (row0, M if akm else K, M, L["TM"], L["WM"], L["blkM"], akm)):
-                        for t in range(TX):
-                            if not step_rows:      # row-major A
-                                rows, kk = in_tile(t, LANE % I, I, blk), LANE // I * KL
-                                off = np.where(kk < kv, rows * K + kk, 0)
-                                at, words = x0 * K + k + off, KL
-                                assert off.max() * size < 1 << 32 and at.max() + words <= M * K
-                            elif bf16:
-                                kr, off, put, _, _ = panel_bf16(I, TX, width, ld, blk)[t]
-                                off = np.where(kr < kv, off, 0)
-                                at = k * ld + x0 + off // 2
-                                assert off.max() < 1 << 32 and at.max() + 8 <= K * X
-                                assert ((at * 2) % 16 == 0).all()
-                                assert put.max() + 16 <= KS * width * 2
-                            else:
-                                kr = LANE // I * 4 + np.arange(4)[:, None]
-                                off = np.where(kr < kv, kr * ld + in_tile(t, LANE % I, I, blk), 0)
-                                at = k * ld + x0 + off
-                                assert off.max() * 4 < 1 << 32 and at.max() < K * X
-                            assert at.min() >= 0
-        if bf16:
-            assert L["W"] * KS * (max(L["WM"], L["WN"]) if akm else L["WN"]) * 2 <= info["lds_bytes"]
+        check_stream(L, info, M, N, K, bf16, akm)
     assert seen >= 20, (seen, tries)
