@@ -140,6 +140,45 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// The same for a C of few rows and many columns, where a square tile is mostly
+// empty: a thread per column and kThinRows rows (blockIdx.y steps over them), B
+// read once per that many rows, A by broadcast. The same chain per output.
+// Bound by B's bytes and the launch.
+constexpr int kThinRows = 4;
+
+template <int DT, bool AK>
+__global__ void __launch_bounds__(256)
+    reference_thin_kernel(const void* __restrict__ Av, const void* __restrict__ Bv,
+                          float* __restrict__ C, int64_t M, int64_t N, int64_t K) {
+  constexpr int U = 8;  // k per round of loads
+  const int64_t row0 = static_cast<int64_t>(blockIdx.y) * kThinRows;
+  int64_t arow[kThinRows];
+#pragma unroll
+  for (int r = 0; r < kThinRows; ++r) arow[r] = min(row0 + r, M - 1) * (AK ? 1 : K);
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t col = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; col < N;
+       col += stride) {
+    float acc[kThinRows] = {};
+    auto step = [&](int64_t k, float b) __attribute__((always_inline)) {
+#pragma unroll
+      for (int r = 0; r < kThinRows; ++r)
+        acc[r] = fmaf(load_in(Av, arow[r] + k * (AK ? M : 1), DT), b, acc[r]);
+    };
+    int64_t k = 0;
+    for (; k + U <= K; k += U) {
+      float b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) b[u] = load_in(Bv, (k + u) * N + col, DT);
+#pragma unroll
+      for (int u = 0; u < U; ++u) step(k + u, b[u]);
+    }
+    for (; k < K; ++k) step(k, load_in(Bv, k * N + col, DT));
+#pragma unroll
+    for (int r = 0; r < kThinRows; ++r)
+      if (row0 + r < M) C[(row0 + r) * N + col] = acc[r];
+  }
+}
+
 // out[2b], out[2b + 1] = block b's max |C − R| and max |R| as bits
 // (non-negative floats order like their bit patterns; a NaN difference wins
 // the max, a NaN of R alone does not count). Bound by HBM. One pair per
@@ -226,6 +265,18 @@ void launch_reference_tiled(const void* A, const void* B, float* C, int64_t M, i
   // of half the size: 1024³ 107 and 79 µs, 2048³ 365 and 290 µs; 418 tiles
   // (1360×1200×720) 78 and 91 µs.
   constexpr int64_t kEnough = 384;
+  // Up to 8 rows against at least a column per thread of one workgroup a CU:
+  // 1×1000003 with K = 1 the tiles took 28 µs, one thread per output 8 and the
+  // thin form 6; 4×1000003 with K = 64 187, 197 and 44; 8×65536 with K = 4096
+  // (fp32) 818, 1841 and 330. Up to 16 rows where K is short: 16×1000003 with
+  // K = 1 37, 33 and 18; with K = 256 720, 3631 and 775. At 16384 columns and
+  // K = 4096 it is the tiles: 4 rows (K-major) 191, 1117 and 297.
+  if (N >= 65536 && (M <= 8 || (M <= 16 && K <= 64))) {
+    const dim3 grid(static_cast<unsigned>(std::min<int64_t>((N + 255) / 256, int64_t{1} << 20)),
+                    static_cast<unsigned>((M + kThinRows - 1) / kThinRows));
+    hipLaunchKernelGGL((reference_thin_kernel<DT, AK>), grid, dim3(256), 0, s, A, B, C, M, N, K);
+    return;
+  }
   const auto tiles = [&](int64_t t) { return (M + t - 1) / t * ((N + t - 1) / t); };
   const auto run = [&](auto tag) {
     constexpr int T = decltype(tag)::value;

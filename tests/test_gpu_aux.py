@@ -1,7 +1,7 @@
 """The helper kernels of the searches' output check at the sizes where their
 work splits: the comparison (one partial result per block, 16-byte and scalar
 loads, remainders, NaN and infinities) and the check product (three tile
-sizes, ragged edges)."""
+sizes, ragged edges, few rows and many columns)."""
 import math
 
 import numpy as np
@@ -60,7 +60,11 @@ def test_compare_at_block_and_alignment_edges(gt, n, offsets):
 # 16 and below it
 REFERENCE = [(1, 1, 1), (31, 33, 15), (32, 32, 16), (33, 31, 17), (65, 1, 33),
              (1024, 1536, 5), (1024, 1472, 6), (1217, 1281, 19), (1281, 1217, 16),
-             (2048, 3072, 3), (2048, 2944, 2), (2433, 2561, 18), (2561, 2433, 1)]
+             (2048, 3072, 3), (2048, 2944, 2), (2433, 2561, 18), (2561, 2433, 1),
+             # few rows and many columns: a whole group of rows and part of one, K
+             # around a round of 8 loads, and the sizes past which the tiles take over
+             (1, 65536, 1), (4, 65537, 7), (5, 65791, 8), (8, 65793, 9), (9, 65536, 64),
+             (16, 65537, 17), (9, 65536, 65), (17, 65536, 8), (8, 65535, 16)]
 
 
 @pytest.mark.parametrize("kmajor", [False, True])
