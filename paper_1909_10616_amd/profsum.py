@@ -130,9 +130,11 @@ def report(out, copy_bytes=1 << 30, extra=""):
            and int(r.get("Grid_Size_Y") or 1) == info["grid_y"]]
     last = sel[-200:]
     dur = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in last]
+    # (the counter files give the whole grid, K slices included)
+    whole = grid * info["grid_y"]
     t = traffic(*(os.path.join(out, d) for d in ("fetch", "write", "cfetch", "cwrite")),
-                copy_bytes, kname, grid, info["lds_bytes"])
-    u, _ = pmc(os.path.join(out, "util"), "u", kname, grid, info["lds_bytes"])
+                copy_bytes, kname, whole, info["lds_bytes"])
+    u, _ = pmc(os.path.join(out, "util"), "u", kname, whole, info["lds_bytes"])
     uc = {cn: v for (k, cn), v in u.items()}
     w = c["workload"]
     flops = 2.0 * c["M"] * c["N"] * c["K"]

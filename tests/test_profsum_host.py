@@ -95,6 +95,28 @@ def test_report_selects_the_last_200_dispatches_of_the_tuned_launch(out):
     assert ratio == round((98500 * 2048 + 65536 * 1024) / 134217728, 2)
 
 
+def test_counters_of_a_split_k_launch(out):
+    """The counter files give a dispatch's whole grid: K slices included."""
+    path = os.path.join(out, "bench_traced.json")
+    text = open(path).read().replace('"grid_y": 1', '"grid_y": 2')
+    open(path, "w").write(text)
+    whole = 2 * GRID_X * 64 * WAVES
+    for d, name, value in (("fetch/k", "FETCH_SIZE", 500.0), ("write/k", "WRITE_SIZE", 300.0),
+                           ("util/u", "SQ_WAIT_ANY", 20.0)):
+        _csv(os.path.join(out, d + "_counter_collection.csv"),
+             _counter_rows(KERNEL, name, [value], grid=whole) + _counter_rows(KERNEL, name, [1.0]))
+    rows = []
+    for i in range(200):
+        rows.append({"Kernel_Name": KERNEL, "Start_Timestamp": 1000 * i, "End_Timestamp": 1000 * i + 500,
+                     "Grid_Size_X": GRID_X * 64 * WAVES, "Grid_Size_Y": 2, "Workgroup_Size_X": 512,
+                     "LDS_Block_Size": 0, "VGPR_Count": 112, "Accum_VGPR_Count": 0,
+                     "SGPR_Count": 112, "Scratch_Size": 0})
+    _csv(os.path.join(out, "trace", "bench_kernel_trace.csv"), rows)
+    md = profsum.report(out)
+    assert md.rstrip().endswith(f"traffic_bytes={500 * 2048 + 300 * 1024}")
+    assert "- SQ_WAIT_ANY: 20" in md
+
+
 def test_best_configuration_for_replay(out):
     assert profsum.best_cfg(os.path.join(out, "bench_traced.json")) == \
         [[16, 2, 8, 16], [128, 1, 1, 32], [16, 4, 2, 32], 16]
