@@ -41,10 +41,13 @@ __device__ __forceinline__ float load_in(const void* p, int64_t i, int dtype) {
 // Every output is one chain of fp32 fused multiply-adds with k ascending,
 // whatever the tile, so the values do not depend on it. It stays off the
 // matrix cores: what it checks runs there.
-// Bound by fp32 VALU issue (one FMA per lane and 4 cycles without packed
-// instructions, 78.6 TFLOP/s): R·R FMAs against 2·R LDS values per k. 4096³
-// bf16: 42.6 ms with one thread per output reading A and B through the
-// caches, 1.75 ms (78 TFLOP/s) with 128×128 tiles; 1024³ 0.47 -> 0.08 ms. Rows,
+// It takes about the sum of its FMAs and of the LDS reads that feed them: R·R FMAs
+// a lane against 2·R LDS values per k, which for the 128×128 tile, four
+// wavefronts and one k is 136 cycles of a CU's FMAs (a register-only loop of
+// v_fmac_f32 reaches 148 TFLOP/s from two wavefronts a SIMD on) and 128 of its LDS
+// (128 bytes a cycle). 4096³ bf16: 42.6 ms with one thread per output reading
+// A and B through the caches, 1.75 ms (78 TFLOP/s, half of that loop) with
+// 128×128 tiles; 1024³ 0.47 -> 0.08 ms. Rows,
 // columns and k past the edges are clamped for the loads (any size, any
 // alignment, scalar coalesced loads: 2·T·KC of them per T·T·KC FMAs) and
 // their products are not formed (k) or not stored (rows, columns).

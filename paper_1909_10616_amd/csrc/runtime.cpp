@@ -39,11 +39,12 @@ int hip_fail(hipError_t e, const char* what) {
 // for each CU and their registers allow, while a part holds min_stages. A
 // workgroup that shares its CU hides its stage boundaries and its C stores
 // behind another's MFMAs; one that takes all of LDS for a deeper ring runs
-// alone, and its grid in rounds. Measured with the most stages that fit and one
-// workgroup a CU against 2 to 4 of them: fp32 4032×960×384 in 945 tiles of
-// 64×64×32 90 -> 34 µs, 2048³ in 512 tiles of 64×128×32 213 -> 157 µs; bf16
-// 2944×1024×4096 in 736 tiles of 64×64×32 91 -> 54 µs, 512×1344×960 in 336
-// tiles of 64×32×64 20.0 -> 13.4 µs.
+// alone, and its grid in rounds. Measured with a ring that keeps others out
+// against this rule's: fp32 4032×960×384 in 945 tiles of 64×64×32 40.3 µs with 8
+// stages (one workgroup a CU), 29.2 with 2 (four); 2048³ in 512 tiles of
+// 64×128×32 148 with 6, 127 with 3; bf16 2944×1024×4096 in 736 tiles of 64×64×32
+// 81.9 with 8 (two), 65.3 with 6 (three); 512×1344×960 in 336 tiles of 64×32×64
+// 15.8 with 8, 11.2 with 6.
 int64_t ring_share_bytes(const Levels& L, int64_t stage_bytes, int64_t min_stages) {
   const int64_t groups = L.gridM * L.gridN * L.kSplit;
   const int64_t by_regs = std::max<int64_t>(1, 4 * (512 / (L.acc + 96)) / L.W);
@@ -52,11 +53,14 @@ int64_t ring_share_bytes(const Levels& L, int64_t stage_bytes, int64_t min_stage
   return kLdsMax / share;
 }
 
-// Ring stages of the fp32 fast path: at most 3 (a fourth and fifth changed
-// nothing: 1024³, one 64×64×64 tile a CU, 27.9, 27.8 and 28.3 µs with 3, 4
-// and 5), 2 where that lets another workgroup in (the 945 tiles above: 44.7 µs
-// with 3 stages and 3 workgroups, 34.0 µs with 2 and 4), 1 where no second
-// fits or K has only one.
+// Ring stages of the fp32 fast path: at most 3 (the third has a wait of its own
+// in the kernel, and more only take LDS: 1024³, one 64×64×64 tile a CU, 25.2,
+// 21.3, 20.5, 21.4 and 21.8 µs with 1 to 5; 512×512×256 in 32×32×32 tiles 9.0,
+// 7.8, 7.4, 8.0 and 8.4; K of four stages, 256³ in 16×16×64 tiles and
+// 512×512×128 in 32×32×32, within 0.5 µs with any), 2 where that lets another
+// workgroup in (worth nothing now: the 945 tiles above 28.6 µs with 3 stages and
+// 3 workgroups, 29.2 with 2 and 4; 2048³ in 64×64×32 tiles 128.9 and 133.8), 1
+// where no second fits or K has only one.
 int64_t f32_ring_stages(const Levels& L, int64_t stage_bytes) {
   return std::max<int64_t>(1, std::min<int64_t>({ring_share_bytes(L, stage_bytes, 2) / stage_bytes,
                                                  L.kLoop, int64_t{3}}));
