@@ -106,8 +106,10 @@ def test_queries_never_crash_on_arbitrary_arguments(gt):
             rc = L.enumerate_configs(ctypes.byref(sp), start, buf, cnt,
                                      ctypes.byref(ctypes.c_uint64()))
         else:
-            rc = L.gt_lower(ctypes.byref(c), _rint(rng), _rint(rng), _rint(rng),
-                            rng.choice([-1, 0, 1, 2, 16, 17, 99]), ctypes.byref(gt.gt_kernel_info()))
+            args = (ctypes.byref(c), _rint(rng), _rint(rng), _rint(rng),
+                    rng.choice([-1, 0, 1, 2, 16, 17, 99]))
+            rc = L.gt_lower(*args, ctypes.byref(gt.gt_kernel_info()))
+            assert L.gt_lower_kernel(*args, ctypes.byref(ctypes.c_int())) == rc
         _expect(gt, rc)
 
 
