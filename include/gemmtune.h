@@ -158,7 +158,8 @@ int gt_measure(const gt_config* cfg, const void* A, const void* B, void* C,
                double* first_ms, int* aborted);
 
 /* Plain (non-MFMA, any M and N) GPU product in fp32, each output one chain of
- * fused multiply-adds with k ascending, used by the search as the reference its candidates are checked against.
+ * fused multiply-adds with k ascending, used by the search as the reference its
+ * candidates are checked against.
  * Same operands and layouts as gemm_run (dtype may carry GT_A_KMAJOR); C is
  * caller-owned M·N fp32. Asynchronous. Errors: GT_EINVAL (null pointer,
  * M, N or K below 1, unknown dtype), GT_EHIP (launch failure). */
@@ -179,7 +180,8 @@ int gt_compare(const void* C, const void* R, int64_t n, void* stream,
  * ends) instead of the buffer gt_compare allocates on first use. No
  * hipMalloc, hipFree or other allocating call is made; n is not limited (at
  * most 1024 blocks reduce any n). Calls that overlap on one GPU race on that
- * array; each call writes what it reads back. Synchronises the stream. GT_EINVAL for null pointers or n < 1, GT_EHIP for a HIP failure. */
+ * array; each call writes what it reads back. Synchronises the stream.
+ * GT_EINVAL for null pointers or n < 1, GT_EHIP for a HIP failure. */
 int gt_compare_noalloc(const void* C, const void* R, int64_t n, void* stream,
                        double* rel);
 

@@ -915,7 +915,7 @@ __device__ __forceinline__ void gemm_fast_dl(const KArgs& a, char* smem) {
 // 20.8 µs; bf16 3136×4096×1024 in 64×256×32 tiles, 8 wavefronts, 186 -> 55 µs,
 // 1024×512×4096 in 64×32×64 tiles 78 -> 28 µs. Against gemm_fast_dl's loop
 // with a branch per load: 512×4096×4096 in 128×64×64 tiles (6 loads a
-// wavefront and stage) 34.8 -> 31 µs; at 2 and 3 loads that loop is up to 12 %
+// wavefront and stage) 34.8 -> 29.6 µs; at 2 and 3 loads that loop is up to 12 %
 // faster (128×2624×3456 in 32×32×32 tiles 32.3 against 36.6 µs), and at the
 // counts it is specialised for 8 % (4096³ in 256×256×32 tiles 115 against
 // 131 µs), so those stay there.

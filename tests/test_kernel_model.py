@@ -570,14 +570,19 @@ def check_generic(L, info, M, N, K, dtype="bf16", akm=False):
 
 @functools.lru_cache(maxsize=None)
 def check_fill(n):
-    """The split-K clear: ≤ 65536 blocks of 256 threads, grid-stride loop;
-    thread f = block·256 + tid writes f, f + stride, … below n."""
-    blocks = min(-(-n // 256), 65536)
-    stride = blocks * 256
-    assert stride <= 2 ** 32 and (stride >= n or blocks == 65536)
-    first = np.arange(stride, dtype=np.int64)
-    # every element of C written exactly once
-    assert int(np.maximum(0, -(-(n - first) // stride)).sum()) == n
+    """The split-K clear: at most 65536 blocks of 256 threads, a grid-stride
+    loop. With C at a 16-byte boundary thread f writes the quads f, f + stride,
+    …, and the first n mod 4 threads an element each of what is left; otherwise
+    thread f the elements f, f + stride, …"""
+    for per in (1, 4):
+        units = n // per
+        blocks = min((n // 4 + 256) // 256 if per == 4 else -(-n // 256), 65536)
+        stride = blocks * 256
+        assert stride <= 2 ** 32 and (stride >= units or blocks == 65536)
+        first = np.arange(stride, dtype=np.int64)
+        # every quad (element) written exactly once, and a thread for every rest
+        assert int(np.maximum(0, -(-(units - first) // stride)).sum()) == units
+        assert n - per * units < min(4, stride)
     return True
 
 
